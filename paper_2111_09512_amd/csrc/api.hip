@@ -1678,24 +1678,17 @@ int ilu_smooth_noalloc(silu_ctx *c, const silu_csr *A, const silu_factors *F, co
 // ---- polynomial Gauss-Seidel smoother --------------------------------------
 namespace {
 
-// Strictly-lower counts of A's rows on the host (copied down), with the
-// pattern and pivot checks.
-int gs_counts(silu_ctx *c, const silu_csr *A, std::vector<int32_t> &counts)
+// Number of strictly lower entries of A, with the pattern and pivot checks;
+// the counts themselves to counts[n] (device) where it is not null.
+int split_count(silu_ctx *c, const silu_csr *A, int32_t *counts, int64_t *total)
 {
     const int64_t n = A->n_rows;
-    counts.assign((size_t)n, 0);
-    if (n == 0) return SILU_OK;
-    int32_t *d_counts = nullptr;
-    HIPCHK(c, hipMalloc(&d_counts, (size_t)n * 4));
-    hipError_t e = launch_init_flags(c->d_flags, 4, INT32_MAX, c->stream);
-    if (e == hipSuccess)
-        e = launch_gs_count((int)n, A->row_ptr, A->col_idx, (const double *)A->val, d_counts, c->d_flags, c->stream);
-    int32_t h[4];
-    if (e == hipSuccess) e = hipMemcpyAsync(counts.data(), d_counts, (size_t)n * 4, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(h, c->d_flags, sizeof(h), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    (void)hipFree(d_counts);
-    if (e != hipSuccess) return hip_fail(c, e);
+    HIPCHK(c, launch_init_flags(c->d_flags, 3, INT32_MAX, c->stream));
+    HIPCHK(c, launch_split_count((int)n, row_lanes(A->nnz, n), A->row_ptr, A->col_idx, (const double *)A->val, counts,
+                                 c->d_flags, c->stream));
+    int32_t h[3];
+    HIPCHK(c, hipMemcpyAsync(h, c->d_flags, sizeof(h), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     if (h[0] != INT32_MAX) {
         c->bad_row = h[0];
         return SILU_ERR_PATTERN;
@@ -1704,6 +1697,7 @@ int gs_counts(silu_ctx *c, const silu_csr *A, std::vector<int32_t> &counts)
         c->bad_row = h[1];
         return SILU_ERR_ZERO_PIVOT;
     }
+    *total = (int64_t)((uint32_t)h[2] - (uint32_t)INT32_MAX); // counted on from INT32_MAX, modulo 2^32
     return SILU_OK;
 }
 
@@ -1715,12 +1709,7 @@ int gs_split_size(silu_ctx *c, const silu_csr *A, int64_t *nnz_lower)
     c->bad_row = -1;
     int st = check_square(A, SILU_F64);
     if (st) return st;
-    std::vector<int32_t> counts;
-    if ((st = gs_counts(c, A, counts))) return st;
-    int64_t t = 0;
-    for (int32_t v : counts) t += v;
-    *nnz_lower = t;
-    return SILU_OK;
+    return split_count(c, A, nullptr, nnz_lower);
 }
 
 int gs_scale_split(silu_ctx *c, const silu_csr *A, silu_factors *G, int flags)
@@ -1734,11 +1723,8 @@ int gs_scale_split(silu_ctx *c, const silu_csr *A, silu_factors *G, int flags)
     if (flags & SILU_VALIDATE) {
         if ((st = validate(c, A, 0))) return st;
     }
-    std::vector<int32_t> counts;
-    if ((st = gs_counts(c, A, counts))) return st;
-    std::vector<int32_t> rp((size_t)n + 1, 0);
-    for (int64_t i = 0; i < n; i++) rp[(size_t)i + 1] = rp[(size_t)i] + counts[(size_t)i];
-    const int64_t nnz = rp[(size_t)n];
+    int64_t nnz = 0;
+    if ((st = split_count(c, A, nullptr, &nnz))) return st;
     if (nnz > 0 && (!G->Ls.col_idx || !G->Ls.val)) return SILU_ERR_ARG;
     // cached copies of earlier values in the output arrays are stale from here on
     if ((st = silu_release(c, G->Ls.row_ptr, G->Ls.col_idx))) return st;
@@ -1749,10 +1735,16 @@ int gs_scale_split(silu_ctx *c, const silu_csr *A, silu_factors *G, int flags)
     G->Us.nnz = 0;
     G->Us.dtype = SILU_F64;
     G->scaled = 3;
-    HIPCHK(c, hipMemcpyAsync(G->Ls.row_ptr, rp.data(), rp.size() * 4, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, launch_gs_fill((int)n, A->row_ptr, A->col_idx, (const double *)A->val, G->Ls.row_ptr, G->Ls.col_idx,
+    // the counts once more, into Gs's row pointers (nothing is written before the checks above), and
+    // their sums; d, written by the fill, holds the tile sums meanwhile
+    const int lanes = row_lanes(A->nnz, n);
+    HIPCHK(c, launch_split_count((int)n, lanes, A->row_ptr, A->col_idx, (const double *)A->val, G->Ls.row_ptr,
+                                 c->d_flags, c->stream));
+    HIPCHK(c, launch_split_scan((int)n, nullptr, G->Ls.row_ptr, (int32_t *)G->d, G->Ls.row_ptr, nullptr, nullptr,
+                                c->stream));
+    HIPCHK(c, launch_gs_fill((int)n, lanes, A->row_ptr, A->col_idx, (const double *)A->val, G->Ls.row_ptr, G->Ls.col_idx,
                              (double *)G->Ls.val, G->d, G->dinv, G->Ls_val32, (int32_t)nnz, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream)); // rp goes out of scope
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     return SILU_OK;
 }
 
@@ -1864,45 +1856,37 @@ int silu_ilu0_fixed_point(silu_ctx *c, const silu_csr *A, int sweeps, silu_csr *
     if (flags & SILU_VALIDATE) {
         if ((st = validate(c, A, 0))) return st;
     }
-    // row counts of the two parts (with the diagonal and pivot checks)
-    std::vector<int32_t> counts;
-    if ((st = gs_counts(c, A, counts))) return st;
-    std::vector<int32_t> rp((size_t)n + 1), Lrp((size_t)n + 1, 0), Urp((size_t)n + 1, 0);
-    HIPCHK(c, hipMemcpyAsync(rp.data(), A->row_ptr, rp.size() * 4, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    for (int64_t i = 0; i < n; i++) {
-        Lrp[(size_t)i + 1] = Lrp[(size_t)i] + counts[(size_t)i];
-        Urp[(size_t)i + 1] = Urp[(size_t)i] + (rp[(size_t)i + 1] - rp[(size_t)i] - counts[(size_t)i]);
-    }
-    const int64_t l_nnz = Lrp[(size_t)n], u_nnz = Urp[(size_t)n];
+    char *w = (char *)ws;
+    double *LU0 = (double *)w, *LU1 = (double *)(w + ws_vec_bytes(nnz));
+    int32_t *tsum = (int32_t *)(w + 2 * ws_vec_bytes(nnz)); // nnz ints
+    int32_t *dpos = (int32_t *)(w + 2 * ws_vec_bytes(nnz) + ws_vec_bytes((nnz + 1) / 2));
+    // row counts of the lower part (with the diagonal and pivot checks), where dpos comes to lie
+    int64_t l_nnz = 0;
+    if ((st = split_count(c, A, dpos, &l_nnz))) return st;
+    const int64_t u_nnz = nnz - l_nnz;
     if ((l_nnz > 0 && (!Ls->col_idx || !Ls->val)) || (u_nnz > 0 && (!U->col_idx || !U->val))) return SILU_ERR_ARG;
     if ((st = silu_release(c, Ls->row_ptr, Ls->col_idx))) return st;
     if ((st = silu_release(c, U->row_ptr, U->col_idx))) return st;
-    char *w = (char *)ws;
-    double *LU0 = (double *)w, *LU1 = (double *)(w + ws_vec_bytes(nnz));
-    int32_t *row_of = (int32_t *)(w + 2 * ws_vec_bytes(nnz));
-    int32_t *dpos = (int32_t *)(w + 2 * ws_vec_bytes(nnz) + ws_vec_bytes((nnz + 1) / 2));
-    HIPCHK(c, launch_init_flags(c->d_flags, 4, INT32_MAX, c->stream));
-    HIPCHK(c, launch_fp_index((int)n, A->row_ptr, A->col_idx, dpos, row_of, c->d_flags, c->stream));
-    HIPCHK(c, launch_fp_init(nnz, A->col_idx, (const double *)A->val, dpos, row_of, LU0, c->stream));
+    const int lanes = row_lanes(nnz, n);
+    HIPCHK(c, launch_split_scan((int)n, A->row_ptr, dpos, tsum, Ls->row_ptr, U->row_ptr, dpos, c->stream));
+    HIPCHK(c, launch_fp_init((int)n, lanes, A->row_ptr, A->col_idx, (const double *)A->val, dpos, LU0, c->stream));
     double *cur = LU0, *nxt = LU1;
     int32_t h[4] = {INT32_MAX, 0, 0, 0};
     for (int sw = 0; sw < sweeps; sw++) {
-        HIPCHK(c, launch_init_flags(c->d_flags + 1, 1, 0, c->stream));
+        // only the last sweep is asked whether it changed anything
+        if (sw == sweeps - 1) HIPCHK(c, launch_init_flags(c->d_flags + 1, 1, 0, c->stream));
         st = timed_launch(c, 8.0 * 3.0 * (double)nnz, [&](const char **nm) {
             *nm = "ilu0_fixed_point_sweep";
-            return launch_fp_sweep(nnz, A->row_ptr, A->col_idx, (const double *)A->val, dpos, row_of, cur, nxt,
+            return launch_fp_sweep((int)n, lanes, A->row_ptr, A->col_idx, (const double *)A->val, dpos, cur, nxt,
                                    c->d_flags, c->stream);
         });
         if (st) return st;
         std::swap(cur, nxt);
     }
-    HIPCHK(c, hipMemcpyAsync(Ls->row_ptr, Lrp.data(), Lrp.size() * 4, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(U->row_ptr, Urp.data(), Urp.size() * 4, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, launch_fp_split((int)n, A->row_ptr, A->col_idx, cur, Ls->row_ptr, Ls->col_idx, (double *)Ls->val,
+    HIPCHK(c, launch_fp_split((int)n, lanes, A->row_ptr, A->col_idx, dpos, cur, Ls->row_ptr, Ls->col_idx, (double *)Ls->val,
                               U->row_ptr, U->col_idx, (double *)U->val, l_nnz, u_nnz, c->stream));
     HIPCHK(c, hipMemcpyAsync(h, c->d_flags, sizeof(h), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream)); // host row pointers go out of scope
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     Ls->n_rows = Ls->n_cols = U->n_rows = U->n_cols = n;
     Ls->nnz = l_nnz;
     U->nnz = u_nnz;

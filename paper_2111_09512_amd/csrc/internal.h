@@ -186,11 +186,26 @@ hipError_t launch_mark_offsets(int n, const int32_t *rp, const int32_t *col, int
                                hipStream_t s);
 hipError_t launch_encode_slots(int n, const int32_t *rp, const int32_t *col, int rpb, int lo, const int32_t *slot_of,
                                uint16_t *code, hipStream_t s);
-// Polynomial Gauss-Seidel set-up: strictly-lower counts (with pattern and
-// pivot flags), then Gs = D^{-1} L, d and dinv.
-hipError_t launch_gs_count(int n, const int32_t *rp, const int32_t *col, const double *val, int32_t *counts,
-                           int32_t *flags, hipStream_t s);
-hipError_t launch_gs_fill(int n, const int32_t *rp, const int32_t *col, const double *val, const int32_t *Grp,
+// Lanes of a wave that set-up kernels put on one row: the power of two nearest
+// above the mean row length, in 8..64, so that a 7-point row (8) and a
+// 27-point row (32) are each read in one round.
+inline int row_lanes(int64_t nnz, int64_t n)
+{
+    const int64_t mean = n > 0 ? (nnz + n - 1) / n : 0;
+    return mean <= 8 ? 8 : (mean <= 16 ? 16 : (mean <= 32 ? 32 : 64));
+}
+// Strictly-lower entries of every row (counts may be null), their total added
+// to flags[2], with pattern (flags[0]) and pivot (flags[1]) flags.
+hipError_t launch_split_count(int n, int lanes, const int32_t *rp, const int32_t *col, const double *val,
+                              int32_t *counts, int32_t *flags, hipStream_t s);
+// Row pointers of the two parts from the lower counts: Lrp (their exclusive
+// sums, [n + 1]) and, where not null, Urp (row_ptr - Lrp) and dpos (the entry
+// of each diagonal).  counts may be Lrp or dpos.  tsum: scan_tiles(n) ints.
+inline int64_t scan_tiles(int64_t n) { return (n + 2047) / 2048; }
+hipError_t launch_split_scan(int n, const int32_t *rp, const int32_t *counts, int32_t *tsum, int32_t *Lrp, int32_t *Urp,
+                             int32_t *dpos, hipStream_t s);
+// Polynomial Gauss-Seidel set-up: Gs = D^{-1} L, d and dinv.
+hipError_t launch_gs_fill(int n, int lanes, const int32_t *rp, const int32_t *col, const double *val, const int32_t *Grp,
                           int32_t *Gcol, double *Gval, double *d, double *dinv, float *G32, int32_t gs_nnz,
                           hipStream_t s);
 // Sliced-ELL set-up: per-slice K and mask bit; fill values and codes.
@@ -212,18 +227,16 @@ hipError_t launch_sub_scaled(int64_t n, double *w, const double *v, const double
 hipError_t launch_div_dev(int64_t n, const double *w, const double *h, double *out, hipStream_t s);
 hipError_t launch_div_host(int64_t n, const double *w, double d, double *out, hipStream_t s);
 hipError_t launch_axpy_host(int64_t n, double alpha, const double *z, double *x, hipStream_t s);
-// ILU(0) by fixed-point sweeps (fixedpoint.hip): diagonal positions and the
-// row of every entry, the initial guess, one synchronous sweep (flags[1] set
-// when a value changed), and the split into Ls and U.
-hipError_t launch_fp_index(int n, const int32_t *rp, const int32_t *col, int32_t *dpos, int32_t *row_of,
-                           int32_t *flags, hipStream_t s);
-hipError_t launch_fp_init(int64_t nnz, const int32_t *col, const double *val, const int32_t *dpos,
-                          const int32_t *row_of, double *LU, hipStream_t s);
-hipError_t launch_fp_sweep(int64_t nnz, const int32_t *rp, const int32_t *col, const double *val, const int32_t *dpos,
-                           const int32_t *row_of, const double *old, double *nw, int32_t *flags, hipStream_t s);
-hipError_t launch_fp_split(int n, const int32_t *rp, const int32_t *col, const double *LU, const int32_t *Lrp,
-                           int32_t *Lcol, double *Lval, const int32_t *Urp, int32_t *Ucol, double *Uval, int64_t l_nnz,
-                           int64_t u_nnz, hipStream_t s);
+// ILU(0) by fixed-point sweeps (fixedpoint.hip): the initial guess, one
+// synchronous sweep (flags[1] set when a value changed), and the split into Ls
+// and U.  dpos: the entry of each row's diagonal; lanes: row_lanes(nnz, n).
+hipError_t launch_fp_init(int n, int lanes, const int32_t *rp, const int32_t *col, const double *val,
+                          const int32_t *dpos, double *LU, hipStream_t s);
+hipError_t launch_fp_sweep(int n, int lanes, const int32_t *rp, const int32_t *col, const double *val,
+                           const int32_t *dpos, const double *old, double *nw, int32_t *flags, hipStream_t s);
+hipError_t launch_fp_split(int n, int lanes, const int32_t *rp, const int32_t *col, const int32_t *dpos,
+                           const double *LU, const int32_t *Lrp, int32_t *Lcol, double *Lval, const int32_t *Urp,
+                           int32_t *Ucol, double *Uval, int64_t l_nnz, int64_t u_nnz, hipStream_t s);
 // Locality relabeling (reorder.hip): order[k] = the row placed at position k,
 // pos = its inverse.  relabel writes row k of N' = Q N Q^T (rp2 given, entries
 // in the original order, columns through pos; col2 may be null to copy values
