@@ -8,9 +8,19 @@
 namespace silu {
 namespace {
 
+// Row scaling: d, dinv and, for every entry right of the diagonal, its column
+// and u_ij / u_ii (u_ij itself with noscale) in Us, FP64 and optionally FP32.
 // flags[0]: first row whose U row does not start with its diagonal (or has
 //           an entry left of it); flags[1]: first row with a zero or
 //           non-finite pivot.  Both start at INT32_MAX.
+//
+// A workgroup takes 256 rows: one lane a row reads the row's range and pivot
+// into LDS, then all lanes stream the rows' entries, each finding its row by a
+// binary search of the 257 row pointers in LDS.  Entries are read and written
+// in order.  20-entry rows, n = 1M (564 MB moved): 1,196 us with one lane a
+// row, a cache line a lane and array; 155 us so, 3.6 TB/s.
+constexpr int SCALE_ROWS = 256;
+constexpr int SCALE_PER = 4; // entries a lane has in flight
 __global__ void __launch_bounds__(256) k_scale_rows(int n, const int32_t *__restrict__ Urp,
                                                     const int32_t *__restrict__ Ucol,
                                                     const double *__restrict__ Uval, int32_t *__restrict__ Usrp,
@@ -19,33 +29,62 @@ __global__ void __launch_bounds__(256) k_scale_rows(int n, const int32_t *__rest
                                                     float *__restrict__ Us32, int noscale, int32_t us_nnz,
                                                     int32_t *flags)
 {
-    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i >= n) return;
-    const int p0 = Urp[i], p1 = Urp[i + 1];
-    if (i == n - 1) Usrp[n] = p1 - n;
-    Usrp[i] = p0 - i;
-    if (p1 <= p0 || Ucol[p0] != i) {
-        atomicMin(&flags[0], i);
-        return;
-    }
-    const double u = Uval[p0];
-    if (!(u != 0.0) || !isfinite(u)) atomicMin(&flags[1], i);
-    d[i] = u;
-    dinv[i] = 1.0 / u;
-    // rows before i each lost exactly their diagonal; a malformed U (flagged
-    // above by the row that lacks it) could shift o, so every store is bounded
-    int o = p0 - i;
-    for (int p = p0 + 1; p < p1; ++p, ++o) {
-        const int j = Ucol[p];
-        if (j <= i) atomicMin(&flags[0], i);
-        if (o < 0 || o >= us_nnz) {
+    __shared__ int32_t rp[SCALE_ROWS + 1];
+    __shared__ double piv[SCALE_ROWS];
+    const int t = (int)threadIdx.x, r0 = (int)blockIdx.x * SCALE_ROWS, nr = min(SCALE_ROWS, n - r0);
+    if (t < nr) {
+        const int i = r0 + t, p0 = Urp[i], p1 = Urp[i + 1];
+        rp[t] = p0;
+        if (t == nr - 1) rp[nr] = p1;
+        if (i == n - 1) Usrp[n] = p1 - n;
+        Usrp[i] = p0 - i;
+        double u = 0.0;
+        if (p1 <= p0 || Ucol[p0] != i) {
             atomicMin(&flags[0], i);
-            continue;
+        } else {
+            u = Uval[p0];
+            if (!(u != 0.0) || !isfinite(u)) atomicMin(&flags[1], i);
+            d[i] = u;
+            dinv[i] = 1.0 / u;
         }
-        const double v = noscale ? Uval[p] : Uval[p] / u;
-        Uscol[o] = j;
-        Usval[o] = v;
-        if (Us32) Us32[o] = (float)v;
+        piv[t] = u;
+    }
+    __syncthreads();
+    const unsigned e1 = (unsigned)rp[nr];
+    for (unsigned eb = (unsigned)(rp[0] + t); eb < e1; eb += 256 * SCALE_PER) {
+        int j[SCALE_PER];
+        double uv[SCALE_PER];
+#pragma unroll
+        for (int k = 0; k < SCALE_PER; ++k) {
+            const unsigned e = eb + 256 * k;
+            j[k] = e < e1 ? Ucol[e] : 0;
+            uv[k] = e < e1 ? Uval[e] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < SCALE_PER; ++k) {
+            const unsigned eu = eb + 256 * k;
+            if (eu >= e1) break;
+            const int e = (int)eu;
+            // the last row that starts at or before e (row pointers that do not ascend are caught by the bounds below)
+            int row = 0;
+#pragma unroll
+            for (int w = SCALE_ROWS / 2; w > 0; w >>= 1)
+                if (row + w < nr && rp[row + w] <= e) row += w;
+            const int i = r0 + row;
+            if (e == rp[row]) continue; // the diagonal, or what the row has in its place
+            if (j[k] <= i) atomicMin(&flags[0], i);
+            // rows before i each lost exactly their diagonal; a malformed U (flagged
+            // by the row that lacks it) could shift o, so every store is bounded
+            const int o = e - i - 1;
+            if (o < 0 || o >= us_nnz) {
+                atomicMin(&flags[0], i);
+                continue;
+            }
+            const double v = noscale ? uv[k] : uv[k] / piv[row];
+            Uscol[o] = j[k];
+            Usval[o] = v;
+            if (Us32) Us32[o] = (float)v;
+        }
     }
 }
 
@@ -581,7 +620,7 @@ hipError_t launch_scale_rows(int n, const int32_t *Urp, const int32_t *Ucol, con
                              int32_t us_nnz, int32_t *flags, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scale_rows, dim3(blocks_for(n, 256)), dim3(256), 0, s, n, Urp, Ucol, Uval, Usrp, Uscol,
+    hipLaunchKernelGGL(k_scale_rows, dim3(blocks_for(n, SCALE_ROWS)), dim3(256), 0, s, n, Urp, Ucol, Uval, Usrp, Uscol,
                        Usval, d, dinv, Us32, noscale, us_nnz, flags);
     return hipGetLastError();
 }

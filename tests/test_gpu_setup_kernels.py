@@ -77,3 +77,22 @@ def test_gauss_seidel_split_rows_of_every_width(orc, B, ctx, n, width, long_rows
     np.testing.assert_array_equal(host(G.d), A.val[A.col == np.repeat(np.arange(n), np.diff(A.row_ptr))])
     np.testing.assert_array_equal(host(G.dinv), dinv)
     np.testing.assert_array_equal(host(G.Ls_val32), Gs.val.astype(np.float32))
+
+
+@pytest.mark.parametrize("scale", [True, False])
+@pytest.mark.parametrize("n,width,long_rows", SHAPES + [(256, 4, ()), (513, 40, (0, 255, 256))])
+def test_scale_factors_rows_of_every_width(orc, B, ctx, n, width, long_rows, scale):
+    say("scale", n, width, long_rows, scale)
+    A = banded(n, width, long_rows, seed=n + width)
+    Ls, U = orc.ilu0(A)
+    d, dinv, Us = orc.scale_rows(U)
+    if not scale:
+        Us.val[:] = U.val[U.col != np.repeat(np.arange(n), np.diff(U.row_ptr))]
+    F = ctx.ilu_scale_factors(B.Csr.from_host(Ls), B.Csr.from_host(U), fp32=True, scale=scale)
+    np.testing.assert_array_equal(host(F.Us.row_ptr), Us.row_ptr)
+    np.testing.assert_array_equal(host(F.Us.col_idx), Us.col)
+    np.testing.assert_array_equal(host(F.Us.val), Us.val)
+    np.testing.assert_array_equal(host(F.Us_val32), Us.val.astype(np.float32))
+    np.testing.assert_array_equal(host(F.Ls_val32), Ls.val.astype(np.float32))
+    np.testing.assert_array_equal(host(F.d), d)
+    np.testing.assert_array_equal(host(F.dinv), dinv)
