@@ -414,7 +414,8 @@ int silu_ilu0_fixed_point(silu_ctx *ctx, const silu_csr *A, int sweeps, silu_csr
  * dot products then sum in the relabeled order), the kernel choices,
  * SILU_VALIDATE; SILU_GRAPH is ignored.  ws: at least
  * silu_fgmres_workspace_size(ctx, n, restart, flags) bytes (2 restart + 6
- * n-vectors, 2 more with SILU_REORDER, and a few KB), 256-byte aligned.  Synchronous (the small
+ * n-vectors, 2 more with SILU_REORDER, and a few KB), 256-byte aligned; the context keeps the products of the
+ * basis besides (restart^2 doubles and at most 2,048 restart more), made on the first solve.  Synchronous (the small
  * least-squares problem is solved on the host every step).  Errors: ARG,
  * SHAPE, NOMEM, UNSUPPORTED (factors neither row- nor row/column-scaled),
  * and those of ilu_smooth.

@@ -163,6 +163,11 @@ struct silu_ctx {
     hipStream_t capture_stream = nullptr; // private, default priority, for graph capture
     bool recording = false;               // launches go into a capture: add up their bytes
     double rec_bytes = 0.0, rec_layout = 0.0;
+    // FGMRES: products and sums of the Arnoldi basis (device) and the fetched
+    // column (pinned), kept from solve to solve and grown where one needs more
+    double *arnoldi = nullptr, *arnoldi_host = nullptr;
+    size_t arnoldi_words = 0, arnoldi_host_words = 0;
+    hipEvent_t arnoldi_event = nullptr;
     bool timing = false;
     std::vector<Pending> pending;
     std::vector<hipEvent_t> free_events;
@@ -1289,6 +1294,9 @@ int silu_destroy(silu_ctx *c)
         (void)hipEventDestroy(p.e1);
     }
     for (auto e : c->free_events) (void)hipEventDestroy(e);
+    (void)hipFree(c->arnoldi);
+    if (c->arnoldi_host) (void)hipHostFree(c->arnoldi_host);
+    if (c->arnoldi_event) (void)hipEventDestroy(c->arnoldi_event);
     (void)hipFree(c->d_flags);
     delete c;
     return SILU_OK;
@@ -1915,6 +1923,29 @@ struct KrylovWs {
     double *gram() const { return h() + m + 2; }                                         // m + 2 scalars
 };
 
+// Room for `words` doubles on the device and `host_words` pinned ones.
+int arnoldi_room(silu_ctx *c, size_t words, size_t host_words)
+{
+    if (!c->arnoldi_event) HIPCHK(c, hipEventCreateWithFlags(&c->arnoldi_event, hipEventDisableTiming));
+    if (words > c->arnoldi_words) {
+        HIPCHK(c, hipStreamSynchronize(c->stream)); // a solve that failed may have left launches behind
+        (void)hipFree(c->arnoldi);
+        c->arnoldi = nullptr;
+        c->arnoldi_words = 0;
+        HIPCHK(c, hipMalloc((void **)&c->arnoldi, words * sizeof(double)));
+        c->arnoldi_words = words;
+    }
+    if (host_words > c->arnoldi_host_words) {
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        if (c->arnoldi_host) (void)hipHostFree(c->arnoldi_host);
+        c->arnoldi_host = nullptr;
+        c->arnoldi_host_words = 0;
+        HIPCHK(c, hipHostMalloc((void **)&c->arnoldi_host, host_words * sizeof(double), hipHostMallocDefault));
+        c->arnoldi_host_words = host_words;
+    }
+    return SILU_OK;
+}
+
 size_t krylov_ws_bytes(int64_t n, int m, int flags)
 {
     const size_t vec = ws_vec_bytes(n);
@@ -1994,11 +2025,25 @@ int fgmres_impl(silu_ctx *c, const silu_csr *A, const silu_factors *F, const dou
         return SILU_OK;
     };
     std::vector<double> H((size_t)(m + 1) * (size_t)m), cs((size_t)m), sn((size_t)m), g((size_t)m + 1),
-        y((size_t)m), hcol((size_t)m + 2);
+        y((size_t)m);
     // eq. nbre: ||x_j||^2 = ||x_0||^2 + 2 y.c + y^T G y with G = Z^T Z, c = Z^T x_0
     const bool nrbe = norm_a > 0.0;
-    std::vector<double> G(nrbe ? (size_t)m * (size_t)m : 0), cz(nrbe ? (size_t)m : 0), yt(nrbe ? (size_t)m : 0),
-        grow(nrbe ? (size_t)m + 2 : 0);
+    std::vector<double> G(nrbe ? (size_t)m * (size_t)m : 0), cz(nrbe ? (size_t)m : 0), yt(nrbe ? (size_t)m : 0);
+    // a cycle's scratch: the products' shares, their sums, and the basis's own products
+    const int mj = std::min(m, max_iters);
+    const int64_t stride = (int64_t)(K.vec / sizeof(double));
+    const size_t nshare = 2 * (size_t)mj * (size_t)arnoldi_blocks(n), nsum = 2 * (size_t)mj;
+    // pinned: a step's h and norm, then the G rows of two steps (one may be under way while the last is read)
+    if ((st = arnoldi_room(c, nshare + nsum + (size_t)mj * (size_t)mj, (size_t)mj + 1 + (nrbe ? 2 * nsum : 0)))) return st;
+    auto grow = [&](int j) { return c->arnoldi_host + mj + 1 + (j & 1) * nsum; };
+    double *const share = c->arnoldi, *const sums = share + nshare, *const St = sums + nsum;
+    auto dots = [&](const double *V, int count, const double *a, const double *bb) {
+        // V once, a and b once for every 8 vectors
+        return timed_launch(c, (8.0 * count + 16.0 * ((count + 7) / 8)) * (double)n, [&](const char **nm) {
+            *nm = "dots";
+            return launch_dots(n, V, stride, count, a, bb, share, c->stream);
+        });
+    };
     double nb = 0.0, beta = 0.0, xx0 = 0.0;
     auto norm_x0 = [&]() -> int { // ||x||^2 of the cycle's start
         int e;
@@ -2020,40 +2065,58 @@ int fgmres_impl(silu_ctx *c, const silu_csr *A, const silu_factors *F, const dou
         *iters = 0;
         return SILU_OK;
     }
+    // direction j: z_j = M^{-1} v_j, one smoother call from z = 0 (z_j cleared before), and w = A z_j
+    auto direction = [&](int j) -> int {
+        double *zj = K.Z(j);
+        int e = ilu_smooth2(c, A, F, K.V(j), zj, outer, m_L, m_U, pflags, K.smoother(), sws_bytes);
+        if (e) return e;
+        if (nrbe) { // row j of G and c_j: z_j . z_i and x . z_i, interleaved
+            if ((e = dots(K.Z(0), j + 1, zj, x))) return e;
+            HIPCHK(c, launch_dots_final(n, j + 1, share, grow(j), c->stream));
+        }
+        return sweep(c, Prec::F64, gA, A, A->val, zj, nullptr, EPI_SPMV, K.w(), nullptr, nullptr, nullptr);
+    };
+    // A step's coefficients decide on the host whether there is a next one.  Its direction needs only
+    // v_{j+1}, so it is enqueued before the wait: the device works on while the host reads and enqueues
+    // (48^3 Poisson operator: 69 us a step with the device idle meanwhile, 45 us so).  The last one is worked out in
+    // vain; on large matrices, where it takes longer than the waits of many steps (10 to 20 us each)
+    // together, it is left until its step is certain.
+    const bool early = A->nnz + F->Ls.nnz + F->Us.nnz <= (int64_t)1 << 24;
     while (k < max_iters) {
         HIPCHK(c, launch_div_host(n, K.V(0), beta, K.V(0), c->stream));
         std::fill(g.begin(), g.end(), 0.0);
         g[0] = beta;
         int j = 0;
-        bool done = false;
+        bool done = false, ahead = false;
+        HIPCHK(c, launch_fill((int)n, K.Z(0), 0.0, nullptr, 0.0, c->stream));
         for (; j < m && k < max_iters; j++) {
-            double *zj = K.Z(j), *w = K.w();
-            // z_j = M^{-1} v_j: one smoother call from z = 0
-            HIPCHK(c, launch_fill((int)n, zj, 0.0, nullptr, 0.0, c->stream));
-            if ((st = ilu_smooth2(c, A, F, K.V(j), zj, outer, m_L, m_U, pflags, K.smoother(), sws_bytes))) return st;
-            if (nrbe) { // row j of G and c_j, fetched with the Hessenberg column
-                for (int i = 0; i <= j; i++)
-                    if ((st = dot(zj, K.Z(i), K.gram() + i, false))) return st;
-                if ((st = dot(zj, x, K.gram() + j + 1, false))) return st;
-                HIPCHK(c, hipMemcpyAsync(grow.data(), K.gram(), sizeof(double) * (size_t)(j + 2),
-                                         hipMemcpyDeviceToHost, c->stream));
-            }
-            // w = A z_j, then modified Gram-Schmidt against v_0..v_j
-            if ((st = sweep(c, Prec::F64, gA, A, A->val, zj, nullptr, EPI_SPMV, w, nullptr, nullptr, nullptr)))
-                return st;
-            for (int i = 0; i <= j; i++) {
-                if ((st = dot(w, K.V(i), K.h() + i, false))) return st;
-                st = timed_launch(c, 24.0 * (double)n, [&](const char **nm) {
-                    *nm = "mgs_update";
-                    return launch_sub_scaled(n, w, K.V(i), K.h() + i, c->stream);
+            double *w = K.w();
+            if (!ahead && (st = direction(j))) return st;
+            // modified Gram-Schmidt of w against v_0..v_j, v_{j+1}, and z_{j+1} = 0
+            const bool next = j + 1 < m && k + 1 < max_iters;
+            double *zn = next ? K.Z(j + 1) : nullptr;
+            if (n <= MGS_SHORT_MAX) {
+                st = timed_launch(c, 8.0 * (j + 3) * (double)n, [&](const char **nm) {
+                    *nm = "mgs_short";
+                    return launch_mgs_short(n, K.V(0), stride, j + 1, w, K.V(j + 1), zn, c->arnoldi_host, c->stream);
                 });
                 if (st) return st;
+            } else {
+                if ((st = dots(K.V(0), j + 1, w, K.V(j)))) return st;
+                HIPCHK(c, launch_project(n, j + 1, share, sums, St, mj, K.h(), c->stream));
+                st = timed_launch(c, 8.0 * (j + 3) * (double)n, [&](const char **nm) {
+                    *nm = "mgs_update";
+                    return launch_subtract(n, K.V(0), stride, j + 1, K.h(), w, K.part(), c->stream);
+                });
+                if (st) return st;
+                HIPCHK(c, launch_normalize(n, w, K.part(), K.h(), j + 1, K.V(j + 1), zn, c->arnoldi_host, c->stream));
             }
-            if ((st = dot(w, w, K.h() + j + 1, true))) return st;
-            if ((st = fetch(hcol.data(), K.h(), j + 2))) return st;
+            HIPCHK(c, hipEventRecord(c->arnoldi_event, c->stream));
+            ahead = next && early;
+            if (ahead && (st = direction(j + 1))) return st;
+            HIPCHK(c, hipEventSynchronize(c->arnoldi_event));
             double *h = &H[(size_t)(m + 1) * (size_t)j];
-            for (int i = 0; i <= j + 1; i++) h[i] = hcol[(size_t)i];
-            if (h[j + 1] != 0.0) HIPCHK(c, launch_div_dev(n, w, K.h() + j + 1, K.V(j + 1), c->stream));
+            for (int i = 0; i <= j + 1; i++) h[i] = c->arnoldi_host[i];
             // Givens rotations on the new column (host; m is small)
             for (int i = 0; i < j; i++) {
                 const double a0 = h[i], a1 = h[i + 1];
@@ -2071,10 +2134,10 @@ int fgmres_impl(silu_ctx *c, const silu_csr *A, const silu_factors *F, const dou
             double xn = 0.0;
             if (nrbe) {
                 for (int i = 0; i <= j; i++) {
-                    G[(size_t)j * (size_t)m + (size_t)i] = grow[(size_t)i];
-                    G[(size_t)i * (size_t)m + (size_t)j] = grow[(size_t)i];
+                    G[(size_t)j * (size_t)m + (size_t)i] = grow(j)[2 * i];
+                    G[(size_t)i * (size_t)m + (size_t)j] = grow(j)[2 * i];
                 }
-                cz[(size_t)j] = grow[(size_t)j + 1];
+                cz[(size_t)j] = grow(j)[2 * j + 1];
                 // y of the first j + 1 steps (back substitution), then the quadratic form
                 for (int i = j; i >= 0; i--) {
                     double t = g[(size_t)i];
@@ -2103,7 +2166,7 @@ int fgmres_impl(silu_ctx *c, const silu_csr *A, const silu_factors *F, const dou
             for (int c2 = i + 1; c2 < j; c2++) t = t - H[(size_t)i + (size_t)(m + 1) * (size_t)c2] * y[(size_t)c2];
             y[(size_t)i] = t / H[(size_t)i + (size_t)(m + 1) * (size_t)i];
         }
-        for (int i = 0; i < j; i++) HIPCHK(c, launch_axpy_host(n, y[(size_t)i], K.Z(i), x, c->stream));
+        HIPCHK(c, launch_combine(n, K.Z(0), stride, j, y.data(), x, c->stream));
         if (done) break;
         if ((st = sweep(c, Prec::F64, gA, A, A->val, x, b, EPI_STORE, K.V(0), nullptr, nullptr, nullptr))) return st;
         if ((st = dot(K.V(0), K.V(0), K.h(), true))) return st;

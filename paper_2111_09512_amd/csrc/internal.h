@@ -219,14 +219,38 @@ hipError_t launch_fill_sliced(int n, int nslice, const int32_t *rp, const int32_
                               void *sval, void *scode, hipStream_t s);
 // Krylov vector kernels (krylov.hip).  launch_dot writes a . b (or its
 // square root) to out[0] on the device, reducing in a fixed order through
-// part[DOT_BLOCKS]; the others update with a device (h[0]) or host scalar.
+// part[DOT_BLOCKS].
 constexpr int DOT_BLOCKS = 1024;
 hipError_t launch_dot(int64_t n, const double *a, const double *b, double *part, double *out, bool take_sqrt,
                       hipStream_t s);
-hipError_t launch_sub_scaled(int64_t n, double *w, const double *v, const double *h, hipStream_t s);
-hipError_t launch_div_dev(int64_t n, const double *w, const double *h, double *out, hipStream_t s);
 hipError_t launch_div_host(int64_t n, const double *w, double d, double *out, hipStream_t s);
-hipError_t launch_axpy_host(int64_t n, double alpha, const double *z, double *x, hipStream_t s);
+// Orthogonalization of one Arnoldi step against v_i = V + i stride, i < count
+// (v_{count-1} the newest).  launch_dots: the shares of arnoldi_blocks(n)
+// workgroups in a . v_i and b . v_i, into part[2 count arnoldi_blocks(n)].
+// launch_dots_final adds them up: dots[2 i] and dots[2 i + 1].
+// launch_project: the same sums for a = w, b = v_{count-1}, then modified
+// Gram-Schmidt's coefficients h[count]; St (ld words a row) keeps the products
+// of the earlier vectors of this basis.  launch_subtract: w -= V h, part[] the
+// shares in w . w; launch_normalize: out = w / ||w|| (left alone if that is 0),
+// zero (or null) cleared, and h with the norm behind it to the pinned words
+// host[count + 1].
+int arnoldi_blocks(int64_t n);
+hipError_t launch_dots(int64_t n, const double *V, int64_t stride, int count, const double *a, const double *b,
+                       double *part, hipStream_t s);
+hipError_t launch_dots_final(int64_t n, int count, const double *part, double *dots, hipStream_t s);
+hipError_t launch_project(int64_t n, int count, const double *part, double *dots, double *St, int ld, double *h,
+                          hipStream_t s);
+hipError_t launch_subtract(int64_t n, const double *V, int64_t stride, int count, const double *h, double *w,
+                           double *part, hipStream_t s);
+hipError_t launch_normalize(int64_t n, const double *w, const double *part, const double *h, int count, double *out,
+                            double *zero, double *host, hipStream_t s);
+// The same three steps in one launch for n <= MGS_SHORT_MAX.
+constexpr int64_t MGS_SHORT_MAX = 4 * DOT_BLOCKS;
+hipError_t launch_mgs_short(int64_t n, const double *V, int64_t stride, int count, const double *w, double *out,
+                            double *zero, double *host, hipStream_t s);
+// x += sum_i y_i (Z + i stride), i ascending, y on the host
+hipError_t launch_combine(int64_t n, const double *Z, int64_t stride, int count, const double *y, double *x,
+                          hipStream_t s);
 // ILU(0) by fixed-point sweeps (fixedpoint.hip): the initial guess, one
 // synchronous sweep (flags[1] set when a value changed), and the split into Ls
 // and U.  dpos: the entry of each row's diagonal; lanes: row_lanes(nnz, n).
