@@ -62,7 +62,7 @@ extern "C" {
 #define SILU_KERNEL_STREAM 0x100  /* CSR-stream sweep kernel (instead of the sliced default)   */
 #define SILU_KERNEL_VECTOR 0x200  /* vector-CSR (lanes-per-row) sweep kernel                */
 #define SILU_KERNEL_BLOCKED 0x400 /* CSR-stream over a row-block partition                  */
-#define SILU_NO_GRAPH 0x800       /* level-scheduled solves: plain launches, no hipGraph     */
+#define SILU_NO_GRAPH 0x800       /* accepted; level-scheduled solves always launch plainly   */
 #define SILU_INDEX32 0x1000       /* sweeps read the 32-bit col_idx, never 16-bit codes      */
 #define SILU_NO_WINDOW 0x2000     /* sweeps never stage the iterate window in LDS            */
 #define SILU_WINDOW 0x4000        /* sweeps stage the window wherever it fits                */
@@ -475,10 +475,12 @@ int silu_nrbe(silu_ctx *ctx, const silu_csr *A, const double *b, const double *x
 
 /*
  * Direct solve T out = rhs by level-set scheduling (Section 4): rows are
- * grouped by the level of the elimination DAG and each level is one kernel
- * launch, rows inside a level in parallel.  The launch sequence is captured
- * once into a hipGraph (cached in the context, keyed by the pointers of T,
- * rhs and out) and replayed; SILU_NO_GRAPH launches the levels one by one.  T: FP64 CSR, lower (uplo =
+ * grouped by the level of the elimination DAG, rows inside a level in
+ * parallel; consecutive narrow levels share a launch, a wide one has its own.
+ * The first solve lays T's pattern out level by level where that pays (many
+ * narrow levels; cached in the context: about 6 bytes an entry, and 8 more for
+ * the values that each solve packs into it).
+ * SILU_NO_GRAPH changes nothing.  T: FP64 CSR, lower (uplo =
  * SILU_LOWER) or upper triangular.  diag = SILU_UNIT: the diagonal is taken
  * as 1 and stored diagonal entries are not read; SILU_NONUNIT: every row must
  * store its diagonal, and the row is divided by it.  rhs, out: FP64 [n],

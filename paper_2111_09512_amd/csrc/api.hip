@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <array>
 #include <climits>
+#include <cmath>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -27,13 +28,63 @@ using namespace silu;
 
 namespace {
 
+// Levels [l0, l1) that are solved together: a run of narrow ones (after far
+// slices [f0, f1) were subtracted), or one wide one (those slices alone).
+struct LevelStep {
+    int l0, l1;
+    bool wide;
+    int f0, f1;
+};
+
 struct LevelInfo {
-    int32_t *d_perm = nullptr;
-    int lanes = 1;                  // lanes per row of the level kernel
-    std::vector<int32_t> level_ptr; // [depth + 1], host
+    int32_t *d_perm = nullptr;      // rows by position (level by level)
+    std::vector<int32_t> level_ptr; // [depth + 1] first position of each level, host
     std::vector<int64_t> level_nnz; // off-diagonal entries per level, host
     int depth = 0;
+    int lanes = 1;                  // lanes per row of the per-level kernel
+    std::vector<int32_t> perm;      // d_perm on the host, until the first solve
+    // the level-ordered copy, made by the first solve where it pays: its structure, and room for one
+    // solve's values (near ones, then far ones) and vectors (right-hand side, solution and a 0, pivots)
+    bool tried = false;
+    LevelSlice *slices = nullptr, *far_slices = nullptr;
+    int32_t *first = nullptr, *far = nullptr, *src = nullptr, *dsrc = nullptr;
+    uint16_t *near = nullptr;
+    double *val = nullptr, *vec = nullptr;
+    int64_t near_slots = 0, far_slots = 0;
+    int max_pairs = 0, max_far_pairs = 0; // of a lane, in slices of a row a lane
+    std::vector<LevelStep> steps;
+    // the last solve that used that room: one on another stream waits for it
+    hipEvent_t used = nullptr;
+    hipStream_t used_on = nullptr;
+    bool ever_used = false;
 };
+
+void free_level_layout(LevelInfo &l)
+{
+    (void)hipFree(l.slices);
+    (void)hipFree(l.far_slices);
+    (void)hipFree(l.first);
+    (void)hipFree(l.far);
+    (void)hipFree(l.src);
+    (void)hipFree(l.dsrc);
+    (void)hipFree(l.near);
+    (void)hipFree(l.val);
+    (void)hipFree(l.vec);
+    if (l.used) (void)hipEventDestroy(l.used);
+    l.slices = l.far_slices = nullptr;
+    l.first = l.far = l.src = l.dsrc = nullptr;
+    l.near = nullptr;
+    l.val = l.vec = nullptr;
+    l.used = nullptr;
+    l.ever_used = false;
+}
+
+void free_levels(LevelInfo &l)
+{
+    free_level_layout(l);
+    (void)hipFree(l.d_perm);
+    l.d_perm = nullptr;
+}
 
 using LevelKey = std::tuple<const void *, const void *, int64_t, int64_t, int>;
 
@@ -126,10 +177,6 @@ void free_compressed(Compressed &C)
     C.wo = nullptr;
 }
 
-// A captured level sequence: one kernel node per level.
-using GraphKey = std::tuple<const void *, const void *, const void *, const void *, const void *, const void *,
-                            const void *, const void *, const void *, const void *, int>;
-
 struct Pending {
     int kid;
     hipEvent_t e0, e1;
@@ -157,7 +204,6 @@ struct silu_ctx {
     std::map<PartKey, Partition> parts;
     std::map<CompKey, Compressed> comp;
     std::map<SlicedKey, Sliced> sliced;
-    std::map<GraphKey, hipGraphExec_t> graphs;
     std::map<SmoothKey, SmoothGraph> smooth_graphs;
     std::map<ReorderKey, Reorder> reorders;
     hipStream_t capture_stream = nullptr; // private, default priority, for graph capture
@@ -1094,89 +1140,270 @@ int get_levels(silu_ctx *c, const silu_csr *T, int uplo, LevelInfo **out)
         (void)hipFree(info.d_perm);
         return hip_fail(c, e);
     }
+    info.perm = std::move(perm);
     auto res = c->levels.emplace(key, std::move(info));
     *out = &res.first->second;
     return SILU_OK;
 }
 
-// Enqueue every level of a level-scheduled substitution on stream s.
-hipError_t enqueue_levels(const LevelArgs &a, const LevelInfo *li, int unit, hipStream_t s)
+// What a solve's steps take, in microseconds.  A run: its launch and that of
+// its far entries, a barrier a level, and its weight (stored entries, rows of
+// them in pairs, and 2.4 a row for the vectors) at the 82 GB/s that one compute
+// unit takes in at 10 bytes an entry.  A level by itself on the copy: a launch.
+// Measured, all of it against a launch per level on the CSR arrays: 1,171
+// levels of 437 rows of 20 entries 1.5 against 4.9 to 6.1 ms, 1,891 of 1,109
+// rows 7.6 against 10.4; 379 of 692 rows of 6 entries (twice) 0.8 against 3.3,
+// 763 of 2,750 rows 5.7 against 12.5; 328 of 4,058 rows of 3 entries the same.
+constexpr double RUN_US = 9.0, RUN_LEVEL_US = 0.4, RUN_WEIGHT_US = 10.0 / 82e3, WIDE_US = 5.5;
+double run_us(int levels, double weight) { return RUN_US + RUN_LEVEL_US * levels + RUN_WEIGHT_US * weight; }
+// A level that alone takes a run longer than a launch of its own is never part of one.
+bool level_is_wide(double weight) { return RUN_LEVEL_US + RUN_WEIGHT_US * weight > WIDE_US; }
+// A solve on the copy also packs and unpacks: about 30 us, and 28 bytes an entry at 3 TB/s.
+double pack_us(int64_t nnz) { return 30.0 + (double)nnz * 28.0 / 3e6; }
+// A launch per level on the CSR arrays, by the mean row length.
+double csr_us(double mean) { return mean <= 4.0 ? 3.7 : (mean <= 12.0 ? 4.3 : 5.2); }
+
+// The level-ordered copy of T (structure) and the steps of a solve; none
+// (li->val stays null) where the per-level kernels are as fast.
+int build_level_layout(silu_ctx *c, const silu_csr *T, LevelInfo *li)
 {
-    for (int l = 0; l < li->depth; l++) {
-        const int start = li->level_ptr[(size_t)l], count = li->level_ptr[(size_t)l + 1] - start;
-        hipError_t e = launch_level(a, unit, li->lanes, start, count, s, nullptr);
-        if (e != hipSuccess) return e;
+    const int64_t n = T->n_rows;
+    const int depth = li->depth;
+    li->tried = true;
+    std::vector<int32_t> perm;
+    perm.swap(li->perm);
+    std::vector<double> weight((size_t)depth);
+    double least = pack_us(T->nnz); // before the ring's limit on runs is known
+    const double csr_total = csr_us((double)T->nnz / (double)n) * depth;
+    for (int l = 0; l < depth; l++) {
+        const double rows = (double)(li->level_ptr[(size_t)l + 1] - li->level_ptr[(size_t)l]);
+        weight[(size_t)l] = rows * (2.0 * std::ceil((double)li->level_nnz[(size_t)l] / rows / 2.0) + 2.4);
+        least += std::min(WIDE_US, run_us(1, weight[(size_t)l]) - RUN_US);
     }
-    return hipSuccess;
+    if (least > csr_total) return SILU_OK;
+    struct Temp { // device scratch of the build
+        void *p[6] = {};
+        ~Temp()
+        {
+            for (void *q : p) (void)hipFree(q);
+        }
+    } tmp;
+    auto up = [&](void **dst, const void *srcp, size_t bytes) {
+        const hipError_t e = hipMalloc(dst, std::max<size_t>(bytes, 8));
+        return e == hipSuccess && srcp ? hipMemcpyAsync(*dst, srcp, bytes, hipMemcpyHostToDevice, c->stream) : e;
+    };
+    std::vector<int32_t> pos((size_t)n), reach((size_t)depth, -1), start((size_t)depth), counts((size_t)n * 2);
+    for (int64_t i = 0; i < n; i++) pos[(size_t)perm[(size_t)i]] = (int32_t)i;
+    HIPCHK(c, up(&tmp.p[0], pos.data(), pos.size() * 4));
+    HIPCHK(c, up(&tmp.p[1], li->level_ptr.data(), li->level_ptr.size() * 4));
+    HIPCHK(c, up(&tmp.p[2], reach.data(), reach.size() * 4));
+    const int32_t *d_pos = (const int32_t *)tmp.p[0], *d_lp = (const int32_t *)tmp.p[1];
+    HIPCHK(c, launch_level_reach((int)n, depth, d_lp, li->d_perm, d_pos, T->row_ptr, T->col_idx, (int32_t *)tmp.p[2],
+                                 c->stream));
+    HIPCHK(c, hipMemcpyAsync(reach.data(), tmp.p[2], reach.size() * 4, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    // runs of narrow levels: whatever a level reads is of this run and still in the ring, or before the run
+    li->steps.clear();
+    double run_weight = 0.0, total = pack_us(T->nnz);
+    auto close_run = [&]() { // levels by themselves where that is faster than the run they would be
+        if (li->steps.empty() || li->steps.back().wide) return;
+        const LevelStep s = li->steps.back();
+        const double as_run = run_us(s.l1 - s.l0, run_weight), apart = WIDE_US * (s.l1 - s.l0);
+        total += std::min(as_run, apart);
+        if (as_run <= apart) return;
+        li->steps.pop_back();
+        for (int l = s.l0; l < s.l1; l++) li->steps.push_back({l, l + 1, true, 0, 0});
+    };
+    for (int l = 0; l < depth; l++) {
+        LevelStep *run = li->steps.empty() || li->steps.back().wide ? nullptr : &li->steps.back();
+        const bool wide = level_is_wide(weight[(size_t)l]);
+        if (!wide && run && reach[(size_t)l] < li->level_ptr[(size_t)run->l0]) {
+            run->l1 = l + 1;
+            run_weight += weight[(size_t)l];
+            continue;
+        }
+        close_run();
+        li->steps.push_back({l, l + 1, wide, 0, 0});
+        run_weight = weight[(size_t)l];
+        if (wide) total += WIDE_US;
+    }
+    close_run();
+    for (const LevelStep &s : li->steps)
+        for (int l = s.l0; l < s.l1; l++) start[(size_t)l] = s.wide ? (int32_t)n : li->level_ptr[(size_t)s.l0];
+    if (total > csr_total) {
+        li->steps.clear();
+        return SILU_OK;
+    }
+    HIPCHK(c, up(&tmp.p[3], start.data(), start.size() * 4));
+    HIPCHK(c, up(&tmp.p[4], nullptr, counts.size() * 4));
+    HIPCHK(c, launch_level_count((int)n, depth, d_lp, (const int32_t *)tmp.p[3], li->d_perm, d_pos, T->row_ptr, T->col_idx,
+                                 (int32_t *)tmp.p[4], c->stream));
+    HIPCHK(c, hipMemcpyAsync(counts.data(), tmp.p[4], counts.size() * 4, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    // slices of one kind over a level's rows; a slice ends at 64 rows, or where its padding would come to
+    // exceed three times its entries
+    std::vector<LevelSlice> slices[2];
+    int64_t pairs[2] = {0, 0};
+    auto cut = [&](int kind, int l, bool keep_empty) {
+        const int64_t a = li->level_ptr[(size_t)l], b = li->level_ptr[(size_t)l + 1];
+        auto add = [&](int64_t row0, int rows, int64_t per) {
+            if (per == 0 && !keep_empty) return;
+            LevelSlice s{};
+            s.off = pairs[kind];
+            s.row0 = (int32_t)row0;
+            s.rows = rows;
+            s.pairs = (int32_t)((per + 1) / 2);
+            s.start = start[(size_t)l];
+            pairs[kind] += (int64_t)s.pairs * (rows < 0 ? 64 : rows);
+            int &most = kind == 0 ? li->max_pairs : li->max_far_pairs;
+            if (rows > 0) most = std::max(most, (int)s.pairs);
+            slices[kind].push_back(s);
+        };
+        int64_t r0 = a, longest = 0, sum = 0;
+        for (int64_t i = a; i < b; i++) {
+            const int64_t len = counts[(size_t)(kind ? n + i : i)];
+            const bool alone = len > LEVEL_LONG_ROW;
+            if (i > r0 && (i - r0 == 64 || alone || std::max(longest, len) * (i - r0 + 1) > 4 * (sum + len) + 256)) {
+                add(r0, (int)(i - r0), longest);
+                r0 = i;
+                longest = sum = 0;
+            }
+            if (alone) { // its 64 lanes take every 64th of the row's entries, of either kind
+                add(i, -1, (counts[(size_t)i] + counts[(size_t)(n + i)] + 1 + 63) / 64);
+                r0 = i + 1;
+                continue;
+            }
+            longest = std::max(longest, len);
+            sum += len;
+        }
+        if (r0 < b) add(r0, (int)(b - r0), longest);
+    };
+    std::vector<int32_t> first((size_t)depth + 1, 0);
+    li->max_pairs = li->max_far_pairs = 0;
+    for (LevelStep &s : li->steps) {
+        s.f0 = (int)slices[1].size();
+        for (int l = s.l0; l < s.l1; l++) {
+            if (!s.wide) cut(0, l, true);
+            cut(1, l, s.wide);
+            first[(size_t)l + 1] = (int32_t)slices[0].size();
+        }
+        s.f1 = (int)slices[1].size();
+    }
+    li->near_slots = 2 * pairs[0];
+    li->far_slots = 2 * pairs[1];
+    const size_t ns = (size_t)li->near_slots, fs = (size_t)li->far_slots;
+    hipError_t e = up((void **)&li->slices, slices[0].data(), slices[0].size() * sizeof(LevelSlice));
+    if (e == hipSuccess) e = up((void **)&li->far_slices, slices[1].data(), slices[1].size() * sizeof(LevelSlice));
+    if (e == hipSuccess) e = up((void **)&li->first, first.data(), first.size() * 4);
+    if (e == hipSuccess) e = up((void **)&li->near, nullptr, ns * 2);
+    if (e == hipSuccess) e = up((void **)&li->far, nullptr, fs * 4);
+    if (e == hipSuccess) e = up((void **)&li->src, nullptr, (ns + fs) * 4);
+    if (e == hipSuccess) e = up((void **)&li->dsrc, nullptr, (size_t)n * 4);
+    if (e == hipSuccess) e = up((void **)&li->val, nullptr, (ns + fs) * 8);
+    if (e == hipSuccess) e = up((void **)&li->vec, nullptr, (size_t)n * 24 + 8);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&li->used, hipEventDisableTiming);
+    if (e == hipSuccess) e = launch_fill(1, li->vec + 2 * n, 0.0, nullptr, 0.0, c->stream); // y[n], for padding
+    if (e == hipSuccess)
+        e = launch_level_fill((int)slices[0].size(), (int)n, 0, li->slices, li->d_perm, d_pos, T->row_ptr, T->col_idx, li->near,
+                              li->src, c->stream);
+    if (e == hipSuccess)
+        e = launch_level_fill((int)slices[1].size(), (int)n, 1, li->far_slices, li->d_perm, d_pos, T->row_ptr, T->col_idx,
+                              li->far, li->src + ns, c->stream);
+    if (e == hipSuccess) e = launch_level_diag((int)n, li->d_perm, T->row_ptr, T->col_idx, li->dsrc, c->stream);
+    const hipError_t e2 = hipStreamSynchronize(c->stream); // the host tables go out of scope
+    if (e == hipSuccess) e = e2;
+    return e == hipSuccess ? SILU_OK : hip_fail(c, e);
 }
 
-int run_levels(silu_ctx *c, const silu_csr *T, LevelInfo *li, int unit, const double *rhs, double *out,
-               const double *dinv, double *s_out, double *xupd, bool graph, const double *dcol = nullptr)
+// out = T^{-1} rhs by levels (out may be null), with the fused s_out = dinv *
+// out and xupd += (dcol) out.  scratch: n doubles for out where it is null.
+int run_levels(silu_ctx *c, const silu_csr *T, LevelInfo *li, int unit, const double *rhs, double *out, double *scratch,
+               const double *dinv, double *s_out, double *xupd, const double *dcol = nullptr)
 {
-    const double xb = dcol ? 24.0 : 16.0; // bytes per row of the x update
-    if (graph && li->depth > 1) {
+    const int64_t n = T->n_rows;
+    int st;
+    if (!li->tried && (st = build_level_layout(c, T, li))) {
+        free_level_layout(*li); // this solve, or later ones, take a launch per level
+        li->steps.clear();
+        (void)hipGetLastError();
+        if (st != SILU_ERR_HIP || c->last_hip != hipErrorOutOfMemory) return st;
+        c->last_hip = hipSuccess;
+    }
+    if (!li->val) { // a launch per level, on the CSR arrays
         LevelArgs a;
         a.perm = li->d_perm;
         a.rp = T->row_ptr;
         a.col = T->col_idx;
         a.val = (const double *)T->val;
         a.rhs = rhs;
-        a.out = out;
+        a.out = out ? out : scratch;
         a.dinv = dinv;
         a.s_out = s_out;
         a.xupd = xupd;
         a.dcol = dcol;
-        GraphKey key{li, T->row_ptr, T->col_idx, T->val, rhs, out, dinv, s_out, xupd, dcol, unit};
-        auto it = c->graphs.find(key);
-        if (it == c->graphs.end()) {
-            if (!c->capture_stream) HIPCHK(c, hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking));
-            HIPCHK(c, hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal));
-            hipError_t e = enqueue_levels(a, li, unit, c->capture_stream);
-            hipGraph_t g = nullptr;
-            hipError_t e2 = hipStreamEndCapture(c->capture_stream, &g);
-            if (e != hipSuccess || e2 != hipSuccess) {
-                if (g) (void)hipGraphDestroy(g);
-                return hip_fail(c, e != hipSuccess ? e : e2);
-            }
-            hipGraphExec_t ex = nullptr;
-            e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(g);
-            if (e != hipSuccess) return hip_fail(c, e);
-            it = c->graphs.emplace(key, ex).first;
-        }
-        double bytes = 0.0;
         for (int l = 0; l < li->depth; l++) {
-            const int count = li->level_ptr[(size_t)l + 1] - li->level_ptr[(size_t)l];
-            bytes += count * (4.0 + 8.0 + 8.0 + 8.0 + 8.0) + 12.0 * (double)li->level_nnz[(size_t)l];
+            const int first = li->level_ptr[(size_t)l], count = li->level_ptr[(size_t)l + 1] - first;
+            double bytes = count * (4.0 + 8.0 + 8.0 + 8.0 + 8.0) + 12.0 * (double)li->level_nnz[(size_t)l];
             if (s_out) bytes += count * 16.0;
-            if (xupd) bytes += count * xb;
+            if (xupd) bytes += count * (dcol ? 24.0 : 16.0);
+            st = timed_launch(c, bytes, [&](const char **nm) {
+                return launch_level(a, unit, li->lanes, first, count, c->stream, nm);
+            });
+            if (st) return st;
         }
-        hipGraphExec_t ex = it->second;
-        return timed_launch(c, bytes, [&](const char **nm) {
-            *nm = "level_graph";
-            return hipGraphLaunch(ex, c->stream);
-        });
+        return SILU_OK;
     }
-    LevelArgs a;
-    a.perm = li->d_perm;
-    a.rp = T->row_ptr;
-    a.col = T->col_idx;
-    a.val = (const double *)T->val;
-    a.rhs = rhs;
-    a.out = out;
-    a.dinv = dinv;
-    a.s_out = s_out;
-    a.xupd = xupd;
-    a.dcol = dcol;
-    for (int l = 0; l < li->depth; l++) {
-        const int start = li->level_ptr[(size_t)l], count = li->level_ptr[(size_t)l + 1] - start;
-        double bytes = count * (4.0 + 8.0 + 8.0 + 8.0 + 8.0) + 12.0 * (double)li->level_nnz[(size_t)l];
-        if (s_out) bytes += count * 16.0;
-        if (xupd) bytes += count * xb;
-        int st = timed_launch(c, bytes, [&](const char **nm) {
-            return launch_level(a, unit, li->lanes, start, count, c->stream, nm);
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
+    if (li->ever_used && li->used_on != c->stream && capture == hipStreamCaptureStatusNone)
+        HIPCHK(c, hipStreamWaitEvent(c->stream, li->used, 0));
+    LevelView L;
+    L.slices = li->slices;
+    L.first = li->first;
+    L.near = li->near;
+    L.val = li->val;
+    L.far_slices = li->far_slices;
+    L.far = li->far;
+    L.far_val = li->val + li->near_slots;
+    L.b = li->vec;
+    L.y = li->vec + n;
+    L.piv = li->vec + 2 * n + 1;
+    const int64_t slots = li->near_slots + li->far_slots;
+    st = timed_launch(c, 20.0 * (double)slots + 20.0 * (double)n, [&](const char **nm) {
+        *nm = "level_pack";
+        return launch_level_pack(slots, (int)n, li->src, (const double *)T->val, li->d_perm, li->dsrc, rhs, li->val, L.b,
+                                 unit ? nullptr : li->vec + 2 * n + 1, c->stream);
+    });
+    if (st) return st;
+    for (const LevelStep &s : li->steps) {
+        double bytes = 0.0;
+        for (int l = s.l0; l < s.l1; l++)
+            bytes += 16.0 * (double)(li->level_ptr[(size_t)l + 1] - li->level_ptr[(size_t)l]) +
+                     12.0 * (double)li->level_nnz[(size_t)l];
+        if (s.f1 > s.f0) {
+            st = timed_launch(c, s.wide ? bytes : 0.0, [&](const char **nm) {
+                *nm = s.wide ? "level_wide" : "level_far";
+                return launch_level_far(L, s.f0, s.f1, s.wide ? 1 : 0, unit, li->max_far_pairs, c->stream);
+            });
+            if (st) return st;
+        }
+        if (s.wide) continue;
+        st = timed_launch(c, bytes, [&](const char **nm) {
+            *nm = "level_run";
+            return launch_level_run(L, s.l0, s.l1, unit, li->max_pairs, c->stream);
         });
         if (st) return st;
+    }
+    st = timed_launch(c, (12.0 + (out ? 8.0 : 0.0) + (s_out ? 16.0 : 0.0) + (xupd ? (dcol ? 24.0 : 16.0) : 0.0)) * (double)n,
+                      [&](const char **nm) {
+                          *nm = "level_unpack";
+                          return launch_level_unpack((int)n, li->d_perm, L.y, out, dinv, s_out, xupd, dcol, c->stream);
+                      });
+    if (st) return st;
+    if (capture == hipStreamCaptureStatusNone) {
+        HIPCHK(c, hipEventRecord(li->used, c->stream));
+        li->used_on = c->stream;
+        li->ever_used = true;
     }
     return SILU_OK;
 }
@@ -1280,11 +1507,10 @@ int silu_destroy(silu_ctx *c)
 {
     if (!c) return SILU_ERR_ARG;
     (void)hipStreamSynchronize(c->stream);
-    for (auto &kv : c->levels) (void)hipFree(kv.second.d_perm);
+    for (auto &kv : c->levels) free_levels(kv.second);
     for (auto &kv : c->parts) (void)hipFree(kv.second.d_blk);
     for (auto &kv : c->comp) free_compressed(kv.second);
     for (auto &kv : c->sliced) free_sliced(kv.second);
-    for (auto &kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
     for (auto &kv : c->smooth_graphs)
         if (kv.second.ex) (void)hipGraphExecDestroy(kv.second.ex);
     for (auto &kv : c->reorders) free_reorder(kv.second);
@@ -1516,12 +1742,11 @@ static int smooth_plain(silu_ctx *c, const silu_csr *A, const silu_factors *F, c
             if ((st = get_levels(c, &F->Ls, SILU_LOWER, &lL))) return st;
             if ((st = get_levels(c, &F->Us, SILU_UPPER, &lU))) return st;
             if ((st = sweep(c, Prec::F64, gA, A, A->val, x, b, EPI_STORE, r, nullptr, nullptr, nullptr))) return st;
-            const bool graph = !(flags & SILU_NO_GRAPH);
-            if ((st = run_levels(c, &F->Ls, lL, 1, (const double *)r, (double *)tmp[0], F->dinv, (double *)s,
-                                 nullptr, graph)))
+            if ((st = run_levels(c, &F->Ls, lL, 1, (const double *)r, nullptr, (double *)tmp[0], F->dinv,
+                                 (double *)s, nullptr)))
                 return st;
-            if ((st = run_levels(c, &F->Us, lU, 1, (const double *)s, (double *)tmp[1], nullptr, nullptr, x, graph,
-                                 dcol)))
+            if ((st = run_levels(c, &F->Us, lU, 1, (const double *)s, nullptr, (double *)tmp[1], nullptr, nullptr,
+                                 x, dcol)))
                 return st;
             continue;
         }
@@ -2319,8 +2544,7 @@ int trisolve_direct(silu_ctx *c, const silu_csr *T, int uplo, int diag, const do
     }
     LevelInfo *li = nullptr;
     if ((st = get_levels(c, T, uplo, &li))) return st;
-    return run_levels(c, T, li, diag == SILU_UNIT ? 1 : 0, rhs, out, nullptr, nullptr, nullptr,
-                      !(flags & SILU_NO_GRAPH));
+    return run_levels(c, T, li, diag == SILU_UNIT ? 1 : 0, rhs, out, nullptr, nullptr, nullptr, nullptr);
 }
 
 int trisolve_iter(silu_ctx *c, const silu_csr *T, const double *dinv, const double *rhs, double *out, int m,
@@ -2397,16 +2621,7 @@ int silu_release(silu_ctx *c, const void *row_ptr, const void *col_idx)
     }
     for (auto it = c->levels.begin(); it != c->levels.end();) {
         if (std::get<0>(it->first) == row_ptr || std::get<1>(it->first) == col_idx) {
-            const LevelInfo *li = &it->second;
-            for (auto g = c->graphs.begin(); g != c->graphs.end();) {
-                if (std::get<0>(g->first) == li) {
-                    (void)hipGraphExecDestroy(g->second);
-                    g = c->graphs.erase(g);
-                } else {
-                    ++g;
-                }
-            }
-            (void)hipFree(it->second.d_perm);
+            free_levels(it->second);
             it = c->levels.erase(it);
         } else {
             ++it;

@@ -344,6 +344,56 @@ struct LevelArgs {
 hipError_t launch_level(const LevelArgs &a, int unit, int lanes, int start, int count, hipStream_t s,
                         const char **name);
 
+// Level-ordered copy of a triangle (trisolve.hip): rows numbered level by
+// level, in slices of up to 64 rows of one level.  A run of levels is solved by
+// one workgroup; an entry is near when its column's position is the run's
+// first, `start`, or later, else far (every entry of a wide level is far).
+constexpr int LEVEL_RING = 20352; // positions whose solution a level run keeps in LDS (159 of the 160 KB)
+constexpr int LEVEL_PAIRS = 10;   // entry pairs a lane holds in registers
+constexpr int LEVEL_LONG_ROW = 256; // a longer row is a slice of its own, shared by 64 lanes
+struct alignas(32) LevelSlice {
+    int64_t off;   // first pair
+    int32_t row0;  // first position
+    int32_t rows;  // rows (one lane each), or -1: one row over 64 lanes
+    int32_t pairs; // entry pairs a lane
+    int32_t start; // position that divides near from far (for the fill); near: then row0 modulo LEVEL_RING
+};
+struct LevelView {
+    const LevelSlice *slices; // of the near entries
+    const int32_t *first;     // [depth + 1] first slice of each level
+    const uint16_t *near;     // position of each near entry's column modulo LEVEL_RING (padding: LEVEL_RING)
+    const double *val;
+    const LevelSlice *far_slices;
+    const int32_t *far;       // position of each far entry's column (padding: n)
+    const double *far_val;
+    double *b;                // right-hand side by position
+    const double *piv;        // pivots by position (UNIT: not read)
+    double *y;                // solution by position, and y[n] = 0
+};
+// reach[level] (start from -1): the largest position that a row of the level
+// reads below the level's end - LEVEL_RING.
+hipError_t launch_level_reach(int n, int depth, const int32_t *level_ptr, const int32_t *perm, const int32_t *pos,
+                              const int32_t *rp, const int32_t *col, int32_t *reach, hipStream_t s);
+// counts[position] = near entries, counts[n + position] = far ones, by start[level]
+hipError_t launch_level_count(int n, int depth, const int32_t *level_ptr, const int32_t *start, const int32_t *perm,
+                              const int32_t *pos, const int32_t *rp, const int32_t *col, int32_t *counts,
+                              hipStream_t s);
+// Codes (near: 16 bits modulo LEVEL_RING; far: positions) and value sources of
+// one kind of slice, and with dsrc the entry of every row's stored diagonal.
+hipError_t launch_level_fill(int nslice, int n, int far_kind, LevelSlice *slices, const int32_t *perm, const int32_t *pos,
+                             const int32_t *rp, const int32_t *col, void *code, int32_t *src, hipStream_t s);
+hipError_t launch_level_diag(int n, const int32_t *perm, const int32_t *rp, const int32_t *col, int32_t *dsrc,
+                             hipStream_t s);
+hipError_t launch_level_pack(int64_t slots, int n, const int32_t *src, const double *val, const int32_t *perm,
+                             const int32_t *dsrc, const double *rhs, double *pval, double *pb, double *piv,
+                             hipStream_t s);
+hipError_t launch_level_unpack(int n, const int32_t *perm, const double *y, double *out, const double *dinv,
+                               double *s_out, double *xupd, const double *dcol, hipStream_t s);
+// Far slices [f0, f1): b -= sums, or with solve the rows' solutions.
+hipError_t launch_level_far(const LevelView &L, int f0, int f1, int solve, int unit, int max_pairs, hipStream_t s);
+// Levels [l0, l1) by one workgroup.
+hipError_t launch_level_run(const LevelView &L, int l0, int l1, int unit, int max_pairs, hipStream_t s);
+
 hipError_t launch_scale_rows(int n, const int32_t *Urp, const int32_t *Ucol, const double *Uval, int32_t *Usrp,
                              int32_t *Uscol, double *Usval, double *d, double *dinv, float *Us32, int noscale,
                              int32_t us_nnz, int32_t *flags, hipStream_t s);

@@ -1,5 +1,5 @@
 // Set-up and auxiliary kernels: row scaling of the U factor, FP32 copies,
-// the level-scheduled substitution step, small vector kernels and a
+// the per-level form of the level-scheduled substitution, small vector kernels and a
 // streaming copy for bandwidth calibration.
 #include "internal.h"
 
