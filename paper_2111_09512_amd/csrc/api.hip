@@ -674,6 +674,8 @@ int build_diag(silu_ctx *c, const silu_csr *N, const void *val, int vbytes, Slic
     S.v.val = S.val;
     S.v.dtab = S.dtab;
     S.v.ndiag = u;
+    S.v.dlo = dtab.front();
+    S.v.dhi = dtab.back();
     S.v.slots = slots;
     S.ok = true;
     *built = true;
@@ -886,6 +888,19 @@ int get_sliced(silu_ctx *c, const silu_csr *N, const void *val, int vbytes, int 
     return SILU_OK;
 }
 
+// Bytes that a sweep of a sliced copy streams, without its epilogue's.
+double sliced_sweep_bytes(Prec p, const Sliced &S, int64_t n)
+{
+    const int vbytes = (p == Prec::F64 || p == Prec::MIX_RES) ? 8 : 4;
+    const double xb = (p == Prec::MIX_L || p == Prec::MIX_U) ? 4.0 : 8.0;
+    const double rb = p == Prec::MIX_U ? 4.0 : 8.0;
+    // row patterns: one byte per row instead of codes; diagonal slices: neither, no slice table
+    const int cb = (S.v.code == 8 || S.v.code == 16) ? 0 : S.v.code;
+    return (double)S.v.slots * (vbytes + cb) + (S.v.code == 16 ? 0.0 : 8.0 * S.v.nslice) + 8.0 * (double)S.masked_rows +
+           (double)n * (xb + rb) + 4.0 * S.v.ndiag +
+           (S.v.code == 8 ? (double)n + 4.0 * S.v.npat * S.v.kp : 0.0);
+}
+
 int sweep(silu_ctx *c, Prec p, SweepGeom g, const silu_csr *N, const void *val, const void *xin,
           const void *rhs, int epi, void *out, const double *dinv, double *x, const double *dshift,
           const double *dcol = nullptr, float *out32 = nullptr)
@@ -901,13 +916,7 @@ int sweep(silu_ctx *c, Prec p, SweepGeom g, const silu_csr *N, const void *val, 
         if (st) return st;
         if (S->ok) {
             g.sl = S->v;
-            const double xb = (p == Prec::MIX_L || p == Prec::MIX_U) ? 4.0 : 8.0;
-            const double rb = p == Prec::MIX_U ? 4.0 : 8.0;
-            // row patterns: one byte per row instead of codes; diagonal slices: neither, no slice table
-            const int cb = (S->v.code == 8 || S->v.code == 16) ? 0 : S->v.code;
-            sliced_bytes = (double)S->v.slots * (vbytes + cb) + (S->v.code == 16 ? 0.0 : 8.0 * S->v.nslice) +
-                           8.0 * (double)S->masked_rows + (double)N->n_rows * (xb + rb) + 4.0 * S->v.ndiag +
-                           (S->v.code == 8 ? (double)N->n_rows + 4.0 * S->v.npat * S->v.kp : 0.0);
+            sliced_bytes = sliced_sweep_bytes(p, *S, N->n_rows);
         } else {
             g.kind = SweepKernel::STREAM; // no entries, too large for the sliced copy, or no structure
             fell_back = true;
@@ -1662,6 +1671,190 @@ int ilu_scale_factors_rowcol(silu_ctx *c, const silu_csr *L, const silu_csr *U, 
     return st;
 }
 
+// ---- several sweeps a launch on small matrices (tile.hip) --------------------
+extern "C++" {
+namespace {
+
+// What a launch takes on the device, in microseconds: a sweep by itself a fixed
+// part and its bytes at the rate of the whole chip; a tile a fixed part, the
+// latency of each round of 1,024 rows that its workgroup makes in a sweep (in a
+// residual more of it) and the bytes of all tiles, the overlap counted as often
+// as it is read.  Measured, 7-point operators, 3/3 steps, L loop / U loop, best
+// tile: 5.6/5.5 us on 16^3 points, 6.2/6.1 on 24^3, 7.1/7.1 on 32^3, 8.5/8.3 on
+// 40^3, 12.5/11.0 on 48^3, 13.9/13.0 on 56^3; with the residual in it the L loop
+// takes 7.6 us on 16^3, 9.2 on 24^3, 13.3 on 32^3 and 20.3 on 40^3, against a
+// launch of 3.3 to 3.8 us for the residual by itself; a sweep by itself takes
+// 3.0 to 3.6 us up to 48^3.  5/5 steps on 32^3: 14.1/12.8.  One workgroup for the
+// call: 7.7 us on 10^3 points, 10 to 14 on 12^3, 19.5 on 16^3.
+//
+// A sequence of calls takes the longer of the two sides: the device with 0.5 us
+// between launches, or the host with 11 us a call and 3 a launch.
+struct TileCost {
+    int launches = 0;
+    double device = 0.0;
+    TileCost operator+(const TileCost &o) const { return {launches + o.launches, device + o.device}; }
+    double us(int outer) const { return std::max(11.0 + 3.0 * launches * outer, (device + 0.5 * launches) * outer); }
+};
+double tile_rounds(int64_t rows) { return std::max(1.0, (double)rows / TILE_THREADS); }
+TileCost sweep_cost(double bytes) { return {1, std::max(3.5, 2.6 + bytes / 4.5e6)}; }
+TileCost tile_cost(double rounds, double all_bytes) { return {1, 3.2 + 1.1 * rounds + all_bytes / 6e6}; }
+double whole_us(int64_t n, int phases) { return 2.6 + 0.8 * phases * tile_rounds(n); }
+
+struct TilePlan {
+    bool whole = false;              // the call in one launch of one workgroup
+    bool lower = false, res = false; // the L loop in a launch, with the residual in it
+    bool upper = false;              // the U loop and the update in a launch
+    TileArgs a{};                    // whole, or the L loop's launch
+    TileArgs u{};                    // the U loop's
+    double lower_bytes[2] = {}, res_bytes[2] = {}, upper_bytes[2] = {}; // algorithmic, layout
+};
+
+// Which sweeps of an iterative call go into tile launches: none unless A, L_s
+// and U~_s are swept in diagonal slices (whose copies this makes, as the sweeps
+// would).
+int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed, int outer, int m_L, int m_U, int flags,
+               const SweepGeom &gA, const SweepGeom &gL, const SweepGeom &gU, TilePlan *P)
+{
+    constexpr int64_t TILE_MAX_ROWS = 1 << 20; // never of use beyond, by the rates above
+    const int64_t n = A->n_rows;
+    const bool diag = gA.kind == SweepKernel::SLICED && gA.slice_code_min < 0 && gL.kind == SweepKernel::SLICED &&
+                      gL.slice_code_min < 0 && gU.kind == SweepKernel::SLICED && gU.slice_code_min < 0;
+    if (!diag || F->scaled == 0 || n > TILE_MAX_ROWS || n < 2 || F->Ls.nnz == 0 || F->Us.nnz == 0) return SILU_OK;
+    const int xb = mixed ? 4 : 8, st_min = -1;
+    Sliced *SA = nullptr, *SL = nullptr, *SU = nullptr;
+    int st;
+    if ((st = get_sliced(c, A, A->val, 8, st_min, &SA))) return st;
+    if ((st = get_sliced(c, &F->Ls, mixed ? (const void *)F->Ls_val32 : F->Ls.val, xb, st_min, &SL))) return st;
+    if ((st = get_sliced(c, &F->Us, mixed ? (const void *)F->Us_val32 : F->Us.val, xb, st_min, &SU))) return st;
+    if (!SA->ok || !SL->ok || !SU->ok || SA->v.code != 16 || SL->v.code != 16 || SU->v.code != 16) return SILU_OK;
+    if (SL->v.dhi >= 0 || SU->v.dlo <= 0) return SILU_OK; // not strictly triangular: the sweeps take it as it is
+    const int wL = -SL->v.dlo, wU = SU->v.dhi;
+    const double rowA = 8.0 * SA->v.ndiag, rowL = (double)xb * SL->v.ndiag, rowU = (double)xb * SU->v.ndiag;
+    const bool zero = (flags & SILU_ZERO_GUESS) != 0 && m_L >= 2;
+    TileArgs a{};
+    a.n = (int)n;
+    a.m_L = m_L;
+    a.m_U = m_U;
+    a.wL = wL;
+    a.wU = wU;
+    a.outer = 1;
+    a.A = {SA->v.val, SA->v.dtab, SA->v.ndiag};
+    a.L = {SL->v.val, SL->v.dtab, SL->v.ndiag};
+    a.U = {SU->v.val, SU->v.dtab, SU->v.ndiag};
+    a.dinv = F->dinv;
+    a.dcol = F->scaled == 2 ? F->dc : nullptr;
+    const double lds = TILE_LDS / 8;
+    auto words = [&](int64_t rows) { return (int64_t)((rows * xb + 7) / 8); };
+    // the L part of a step (residual and L loop) and the U part, each as sweeps by themselves or as the
+    // fastest tile size of each form; then the best pair of forms
+    struct Option {
+        bool tiled;
+        TileCost cost;
+        TileArgs args;
+    };
+    const TileCost resA = sweep_cost(n * (rowA + 24.0)), one_L = sweep_cost(n * (rowL + 3.0 * xb)),
+                   one_U = sweep_cost(n * (rowU + 3.0 * xb));
+    Option low[3] = {{false, resA, a}, {false, {}, a}, {false, {}, a}}, up[2] = {{false, {}, a}, {false, {}, a}};
+    for (int k = 2; k <= m_L; k++) low[0].cost = low[0].cost + one_L;
+    for (int k = 2; k <= m_U; k++) up[0].cost = up[0].cost + one_U;
+    if (m_L == 1 && m_U == 1) up[0].cost = {1, 3.5}; // the update
+    auto better = [](Option &o, const TileCost &cost) {
+        if (o.tiled && cost.device >= o.cost.device) return false;
+        o.tiled = true;
+        o.cost = cost;
+        return true;
+    };
+    for (int tile = 128; tile < n; tile *= 2) {
+        const int64_t tiles = (n + tile - 1) / tile;
+        if (tiles > 256) continue;
+        // the L loop: r on `back` rows more than its own, y_k on one reach less each (m_U = 1: its last
+        // sweep updates x, which the sweep by itself does in its epilogue)
+        if (m_L >= 2 && m_U >= 2 && (int64_t)(m_L - 1) * wL + tile < INT32_MAX / 2) {
+            const int back = (m_L - 1) * wL;
+            const int64_t rl = std::min<int64_t>(n, tile + back), bl = m_L >= 3 ? std::min<int64_t>(n, tile + back - wL) : 0;
+            // y_2 stands in buf[1]; buf[0] is there from y_3 (m_L = 3: s goes straight out)
+            const int64_t nb = m_L >= 4 ? 2 : (m_L == 3 ? 1 : 0);
+            double sweeps = 0.0, rounds = 0.0;
+            for (int k = 2; k <= m_L; k++) {
+                const int64_t rows = std::min<int64_t>(n, tile + (int64_t)(m_L - k) * wL);
+                if (k == 2) sweeps = rows * rowL; // then they are near
+                rounds += tile_rounds(rows);
+            }
+            for (int res = 0; res < 2 && (double)(rl + nb * words(bl)) <= lds; res++) {
+                const TileCost t = tile_cost(rounds + (res ? 1.5 * tile_rounds(rl) : 0.0),
+                                             tiles * (sweeps + rl * (res ? rowA + 16.0 : 8.0)));
+                Option &o = low[1 + res];
+                if (!better(o, res ? t : resA + t)) continue;
+                o.args.tile = tile;
+                o.args.lower = 1;
+                o.args.residual = res;
+                o.args.zero = zero;
+                o.args.back = back;
+                o.args.buf1 = (int)rl;
+                o.args.buf0 = (int)(rl + words(bl));
+            }
+        }
+        if (m_U >= 3 && (int64_t)(m_U - 1) * wU + tile < INT32_MAX / 2) {
+            const int ahead = (m_U - 1) * wU;
+            const int64_t bl = std::min<int64_t>(n, tile + ahead);
+            double bytes = bl * (double)xb, rounds = 0.0;
+            for (int k = 2; k <= m_U; k++) {
+                const int64_t rows = std::min<int64_t>(n, tile + (int64_t)(m_U - k) * wU);
+                if (k == 2) bytes += rows * rowU;
+                rounds += tile_rounds(rows);
+            }
+            const int64_t third = m_U >= 4 ? words(bl) : 0; // r's place
+            if ((double)(third + 2 * words(bl)) <= lds && better(up[1], tile_cost(rounds, tiles * bytes))) {
+                TileArgs &u = up[1].args;
+                u.tile = tile;
+                u.upper = 1;
+                u.ahead = ahead;
+                u.buf0 = (int)third;
+                u.buf1 = (int)(third + words(bl));
+            }
+        }
+    }
+    double best = (low[0].cost + up[0].cost).us(outer);
+    for (int l = 0; l < 3; l++)
+        for (int u = 0; u < 2; u++) {
+            if ((l && !low[l].tiled) || (u && !up[u].tiled)) continue;
+            const double t = (low[l].cost + up[u].cost).us(outer);
+            if (t >= best) continue;
+            best = t;
+            P->lower = l > 0;
+            P->res = l == 2;
+            P->a = low[l].args;
+            P->upper = u > 0;
+            P->u = up[u].args;
+        }
+    if ((double)(n + 2 * words(n)) <= lds && std::max(11.0 + 3.0, 0.5 + whole_us(n, outer * (m_L + m_U))) < best) {
+        P->whole = true;
+        P->a = a;
+        P->a.tile = (int)n;
+        P->a.lower = P->a.upper = P->a.residual = 1;
+        P->a.outer = outer;
+        P->a.zero = zero;
+        P->a.back = P->a.ahead = 0; // everything is its own
+        P->a.buf0 = (int)n;
+        P->a.buf1 = (int)(n + words(n));
+    }
+    // the sweeps' bytes, as they are credited one by one
+    const Prec pL = mixed ? Prec::MIX_L : Prec::F64, pU = mixed ? Prec::MIX_U : Prec::F64;
+    auto credit = [&](double *to, Prec p, const silu_csr *N, const Sliced &S, int epi) {
+        const double col = a.dcol && (epi == EPI_UPDATE || epi == EPI_SCALE_UPDATE) ? 8.0 * n : 0.0;
+        to[0] += sweep_bytes(p, n, N->nnz, epi, false, 4.0) + col;
+        to[1] += sliced_sweep_bytes(p, S, n) + epi_bytes(p, n, epi, false) + col;
+    };
+    credit(P->res_bytes, Prec::F64, A, *SA, m_L >= 2 ? EPI_STORE : EPI_SCALE);
+    for (int k = 2; k <= m_L; k++)
+        credit(P->lower_bytes, pL, &F->Ls, *SL, k < m_L ? EPI_STORE : (m_U >= 2 ? EPI_SCALE : EPI_SCALE_UPDATE));
+    for (int k = 2; k <= m_U; k++) credit(P->upper_bytes, pU, &F->Us, *SU, k < m_U ? EPI_STORE : EPI_UPDATE);
+    return SILU_OK;
+}
+
+} // namespace
+} // extern "C++"
+
 static int smooth_plain(silu_ctx *c, const silu_csr *A, const silu_factors *F, const double *b, double *x,
                         int outer_sweeps, int m_L, int m_U, int flags, void *ws, size_t ws_bytes)
 {
@@ -1735,6 +1928,22 @@ static int smooth_plain(silu_ctx *c, const silu_csr *A, const silu_factors *F, c
     const void *Uval = mixed ? (const void *)F->Us_val32 : F->Us.val;
     const int to_s = scaled ? EPI_SCALE : EPI_STORE;
     const int to_x = scaled ? EPI_SCALE_UPDATE : EPI_UPDATE;
+    TilePlan T;
+    if (!direct && (st = plan_tiles(c, A, F, mixed, outer_sweeps, m_L, m_U, flags, gA, gL, gU, &T))) return st;
+    if (T.whole) {
+        TileArgs t = T.a;
+        t.rhs = b;
+        t.x = x;
+        double by[2];
+        for (int k = 0; k < 2; k++)
+            by[k] = outer_sweeps * (T.res_bytes[k] + T.lower_bytes[k] + T.upper_bytes[k]) - (t.zero ? T.res_bytes[k] : 0.0);
+        st = timed_launch(c, by[0], by[1], [&](const char **nm) {
+            *nm = "smooth_tile";
+            return launch_smooth_tile(t, mixed ? 1 : 0, c->stream);
+        });
+        if (st) return st;
+        return (flags & SILU_CHECK_FINITE) ? check_finite(c, n, x) : SILU_OK;
+    }
 
     for (int it = 0; it < outer_sweeps; it++) {
         if (direct) {
@@ -1759,13 +1968,14 @@ static int smooth_plain(silu_ctx *c, const silu_csr *A, const silu_factors *F, c
         // extra store only costs there: 1.35 against 1.33 ms per application on the relabeled
         // random operator of 16.8M rows.)
         bool split = false;
-        if (mixed && m_L >= 2 && gL.kind == SweepKernel::SLICED) {
+        const bool b_is_r = m_L >= 2 && it == 0 && (flags & SILU_ZERO_GUESS) != 0;
+        if (mixed && m_L >= 2 && !T.lower && gL.kind == SweepKernel::SLICED) {
             Sliced *SL = nullptr;
             if ((st = get_sliced(c, &F->Ls, Lval, 4, gL.slice_code_min, &SL))) return st;
             split = SL->ok;
         }
         const void *rr = r, *y1 = nullptr;
-        if (m_L >= 2 && it == 0 && (flags & SILU_ZERO_GUESS)) {
+        if (b_is_r || (T.lower && T.res)) {
             rr = b;
             st = SILU_OK;
         } else if (split) {
@@ -1791,7 +2001,22 @@ static int smooth_plain(silu_ctx *c, const silu_csr *A, const silu_factors *F, c
         }
         // L sweeps: y_1 = r, y_k = r - Ls y_{k-1}
         const void *cur = y1 ? y1 : rr;
-        for (int k = 2; k <= m_L; k++) {
+        if (T.lower) { // all of them, with the residual or from r
+            TileArgs t = T.a;
+            t.rhs = (const double *)rr;
+            t.x = x;
+            t.s_out = s;
+            t.residual = T.res && !b_is_r;
+            t.zero = 0;
+            double by[2];
+            for (int k = 0; k < 2; k++) by[k] = T.lower_bytes[k] + (t.residual ? T.res_bytes[k] : 0.0);
+            st = timed_launch(c, by[0], by[1], [&](const char **nm) {
+                *nm = "smooth_tile";
+                return launch_smooth_tile(t, mixed ? 1 : 0, c->stream);
+            });
+            if (st) return st;
+        }
+        for (int k = 2; k <= m_L && !T.lower; k++) {
             const bool last = k == m_L;
             void *out = last ? s : tmp[k & 1];
             int epi = last ? (m_U >= 2 ? to_s : to_x) : EPI_STORE;
@@ -1803,6 +2028,17 @@ static int smooth_plain(silu_ctx *c, const silu_csr *A, const silu_factors *F, c
                        F->dinv, x, nullptr, dcol);
             if (st) return st;
             cur = out;
+        }
+        if (T.upper) {
+            TileArgs t = T.u;
+            t.x = x;
+            t.s_in = s;
+            st = timed_launch(c, T.upper_bytes[0], T.upper_bytes[1], [&](const char **nm) {
+                *nm = "smooth_tile";
+                return launch_smooth_tile(t, mixed ? 1 : 0, c->stream);
+            });
+            if (st) return st;
+            continue;
         }
         // U sweeps: z_1 = s, z_k = s - Us z_{k-1}; the last adds z to x
         cur = s;

@@ -72,6 +72,7 @@ struct SlicedView {
     int32_t wst[PAT_WIN_MAX] = {};
     const uint16_t *ltab = nullptr;  // [npat * kl]
     const int32_t *wflag = nullptr;  // [nslice] 1: the slice's rows lie on the windows
+    int dlo = 0, dhi = 0; // code 16: the first and the last diagonal
     // code 16 (diagonal slices, FP64 or FP32 values): every row of the matrix lies
     // on the ndiag <= DIAG_MAX diagonals dtab[] (ascending); nslice slices of
     // 128 rows, slot k of row r holding its entry on diagonal dtab[k] (0 where
@@ -290,6 +291,32 @@ SweepGeom pick_geom(int64_t n, int64_t nnz, int flags);
 int make_owned_sliced(silu_ctx *c, const silu_csr *N, const void *val, int vbytes, SlicedView *view, void **owner);
 void free_owned_sliced(void *owner);
 hipError_t launch_sweep(Prec p, const SweepGeom &g, const SweepArgs &a, hipStream_t s, const char **name);
+
+// Several sweeps of the smoother in one launch (tile.hip), on diagonal slices.
+constexpr int TILE_THREADS = 1024;
+constexpr int TILE_LDS = 160 * 1024;
+struct TileMatrix {
+    const void *val;
+    const int32_t *dtab; // ascending
+    int u;
+};
+struct TileArgs {
+    int n, tile;         // a workgroup owns `tile` rows
+    int lower, residual; // run the L loop, and the residual before it (else rhs is r)
+    int upper;           // run the U loop and the update (lower and upper: one workgroup)
+    int outer, zero;     // outer steps (1 unless lower and upper); the first residual is rhs
+    int m_L, m_U;
+    int wL, wU;          // how far a row of L_s reads back, and one of U_s on
+    int back, ahead;     // rows before and behind its own that a workgroup takes in
+    int buf0, buf1;      // the iterates' buffers, in words of the LDS (r at 0)
+    TileMatrix A, L, U;
+    const double *rhs;
+    double *x;
+    const double *dinv, *dcol;
+    void *s_out;         // lower alone: s
+    const void *s_in;    // upper alone: s
+};
+hipError_t launch_smooth_tile(const TileArgs &a, int fp32, hipStream_t s);
 
 // Batched sweeps of one precision (serving): d_ops[i] is one request's sweep,
 // d_first[i] its first workgroup (ceil(n_i / SERVE_TILE_ROWS) workgroups
