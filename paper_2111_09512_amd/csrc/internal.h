@@ -326,13 +326,20 @@ hipError_t launch_smooth_tile(const TileArgs &a, int fp32, hipStream_t s);
 constexpr int SERVE_TILE_ROWS = 256;
 hipError_t launch_sweep_batch(Prec p, const SweepArgs *d_ops, const int32_t *d_first, int nops, int total,
                               hipStream_t s);
+// The same for ops on shared matrices: group i is the ops [d_start[i],
+// d_start[i + 1]) -- one, or up to GROUP_OPS without checks whose sv is the same
+// row-pattern copy -- and d_first[i] its first workgroup (as many as one of its ops has).
+constexpr int GROUP_OPS = 8;
+hipError_t launch_sweep_groups(Prec p, const SweepArgs *d_ops, const int32_t *d_first, const int32_t *d_start, int groups,
+                               int total, hipStream_t s);
 // The same with the op table passed in the kernel arguments (no copy to the
 // device first): at most BATCH_ARG_OPS ops.
 constexpr int BATCH_ARG_OPS = 24;
 struct BatchArgs {
     SweepArgs op[BATCH_ARG_OPS];
-    int32_t first[BATCH_ARG_OPS + 1];
-    int nops;
+    int32_t first[BATCH_ARG_OPS + 1]; // of the groups
+    int32_t start[BATCH_ARG_OPS + 1];
+    int nops, groups; // as many: every op by itself
 };
 hipError_t launch_sweep_batch_args(Prec p, const BatchArgs &b, hipStream_t s);
 

@@ -27,6 +27,7 @@
 #include <cmath>
 #include <cstring>
 #include <deque>
+#include <functional>
 #include <map>
 #include <unordered_map>
 #include <new>
@@ -64,6 +65,7 @@ struct Matrix {
     const SlicedView *sv[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
     void *own[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
     SlicedView *d_views = nullptr;
+    bool patterns[5] = {}; // the copy is of row patterns
     bool fp32 = false; // the factors carry FP32 values
 };
 
@@ -138,8 +140,9 @@ struct Record {
 // device before the step's launches.
 struct StagedGroup {
     Prec kind;
-    size_t ops_off, first_off; // in the staging buffer
+    size_t ops_off, first_off; // in the staging buffer; the groups' first ops follow the first_off table
     int k, total;
+    int groups; // k: every op by itself
 };
 struct StepPlan {
     int t = 0;
@@ -148,6 +151,9 @@ struct StepPlan {
     int count[5] = {0, 0, 0, 0, 0};
     StagedGroup sg[5];
     int nsg = 0;
+    std::vector<uint8_t> grouped; // the op may share a workgroup: row patterns, no check
+    std::vector<int> order;       // group_ops: the ops of one precision, those on one matrix together
+    std::vector<int32_t> start;   // and the first op of each group
 };
 const Prec KINDS[5] = {Prec::F64, Prec::MIX_RES, Prec::MIX_L1, Prec::MIX_L, Prec::MIX_U};
 
@@ -405,8 +411,9 @@ SweepArgs op_of(const silu_server *s, const Request &q, Prec *prec = nullptr)
 }
 
 // Bytes of one staging buffer for cap ops over at most 5 groups: each group's
-// ops, then its cap + 1 first-block offsets, the group rounded up to 16 bytes.
-size_t stage_bytes(int cap) { return (size_t)cap * (sizeof(SweepArgs) + sizeof(int32_t)) + 5 * 32; }
+// ops, then at most its cap + 1 first-block offsets and as many first ops, the
+// group rounded up to 16 bytes.
+size_t stage_bytes(int cap) { return (size_t)cap * (sizeof(SweepArgs) + 2 * sizeof(int32_t)) + 5 * 32; }
 
 size_t align16(size_t b) { return (b + 15) & ~(size_t)15; }
 
@@ -693,7 +700,10 @@ int silu_server_register(silu_server *s, const silu_csr *A, const silu_factors *
         free_matrix_copies(M);
         return st != SILU_OK ? st : fail(s, e);
     }
-    for (int k = 0; k < 5; k++) M.sv[k] = views[k].nslice > 0 ? M.d_views + k : nullptr;
+    for (int k = 0; k < 5; k++) {
+        M.sv[k] = views[k].nslice > 0 ? M.d_views + k : nullptr;
+        M.patterns[k] = M.sv[k] && views[k].code == 8;
+    }
     s->mats.push_back(M);
     *matrix_id = (int)s->mats.size() - 1;
     return SILU_OK;
@@ -798,10 +808,13 @@ void plan_step(const silu_server *s, int t, StepPlan &p)
     p.nsg = 0;
     p.ops.resize((size_t)nops);
     p.prec.resize((size_t)nops);
+    p.grouped.resize((size_t)nops);
     for (int i = 0; i < nops; i++) {
         Request q = s->active[(size_t)i];
         q.op += t;
-        p.ops[(size_t)i] = op_of(s, q, &p.prec[(size_t)i]);
+        const SweepArgs a = p.ops[(size_t)i] = op_of(s, q, &p.prec[(size_t)i]);
+        const Matrix &M = s->mats[(size_t)q.mid];
+        p.grouped[(size_t)i] = a.sv && M.patterns[a.sv - M.d_views] && !a.scheck;
     }
     for (int g = 0; g < 5; g++) p.count[g] = 0;
     for (int i = 0; i < nops; i++)
@@ -815,51 +828,98 @@ bool plan_staged(const StepPlan &p)
     return false;
 }
 
+// The plan's ops of one precision in launch order (p.order), cut into groups
+// that share their workgroups: first[i] the first workgroup of group i, start[i]
+// its first op (each with an end).  first must hold an entry more than there
+// are ops.  Returns the number of groups.
+//
+// Ops on the same row-pattern copy share the reads of its values and pattern
+// codes: 33 of the 57 bytes that a sweep of a 7-point factor moves a row.  A
+// group takes at most GROUP_OPS of them, and fewer where the launch would not
+// be left with GROUP_TILES workgroups times the ops of a group: 64 requests on
+// 6 matrices of up to 64^3 points, 5.8 million rows a sweep, take 70 us each by
+// themselves and 43 in groups of up to 8 (1.40 -> 1.12 ms for all their
+// sweeps; in groups of up to 4, 1.14); 40 requests on 3 matrices of up to 48^3
+// points 679, 611 and 594 us in groups of 1, 3 and 4, 621 in groups of 8; 24
+// requests on matrices of up to 32^3 points take 308 us either way.
+constexpr int64_t GROUP_TILES = 1536;
+int group_ops(StepPlan &p, Prec kind, int32_t *first)
+{
+    std::vector<int> &order = p.order;
+    std::vector<int32_t> &start = p.start;
+    order.clear();
+    start.clear();
+    int64_t tiles = 0;
+    for (int i = 0; i < (int)p.ops.size(); i++) {
+        if (p.prec[(size_t)i] != kind) continue;
+        order.push_back(i);
+        tiles += (p.ops[(size_t)i].n + SERVE_RPB - 1) / SERVE_RPB;
+    }
+    const int most = (int)std::min<int64_t>(std::max<int64_t>(tiles / GROUP_TILES, 1), GROUP_OPS);
+    auto copy = [&](int i) { return p.grouped[(size_t)i] ? p.ops[(size_t)i].sv : nullptr; };
+    if (most > 1)
+        std::stable_sort(order.begin(), order.end(),
+                         [&](int i, int j) { return std::less<const SlicedView *>()(copy(i), copy(j)); });
+    const int k = (int)order.size();
+    int groups = 0, total = 0;
+    for (int at = 0; at < k;) {
+        const SweepArgs &op = p.ops[(size_t)order[(size_t)at]];
+        int run = 1;
+        if (most > 1 && copy(order[(size_t)at]))
+            while (at + run < k && copy(order[(size_t)(at + run)]) == op.sv) run++;
+        const int parts = (run + most - 1) / most; // of nearly the same size
+        for (int j = 0; j < parts; j++) {
+            first[groups++] = total;
+            start.push_back(at + (int)((int64_t)run * j / parts));
+            total += (op.n + SERVE_RPB - 1) / SERVE_RPB;
+        }
+        at += run;
+    }
+    first[groups] = total;
+    start.push_back(k);
+    return groups;
+}
+
 // The plan's staged groups packed into buf from *used on.
 void pack_step(StepPlan &p, char *buf, size_t *used)
 {
-    const int nops = (int)p.ops.size();
     for (int g = 0; g < 5; g++) {
         if (p.count[g] <= BATCH_ARG_OPS) continue;
-        const size_t first_off = *used + sizeof(SweepArgs) * (size_t)p.count[g];
+        const int k = p.count[g];
+        const size_t first_off = *used + sizeof(SweepArgs) * (size_t)k;
         SweepArgs *h_ops = (SweepArgs *)(buf + *used);
         int32_t *h_first = (int32_t *)(buf + first_off);
-        int k = 0, total = 0;
-        for (int i = 0; i < nops; i++) {
-            if (p.prec[(size_t)i] != KINDS[g]) continue;
-            h_ops[k] = p.ops[(size_t)i];
-            h_first[k++] = total;
-            total += (p.ops[(size_t)i].n + SERVE_RPB - 1) / SERVE_RPB;
-        }
-        h_first[k] = total;
-        p.sg[p.nsg++] = {KINDS[g], *used, first_off, k, total};
-        *used = align16(first_off + sizeof(int32_t) * (size_t)(k + 1));
+        const int groups = group_ops(p, KINDS[g], h_first);
+        for (int i = 0; i < k; i++) h_ops[i] = p.ops[(size_t)p.order[(size_t)i]];
+        if (groups < k) std::copy(p.start.begin(), p.start.end(), h_first + groups + 1);
+        p.sg[p.nsg++] = {KINDS[g], *used, first_off, k, h_first[groups], groups};
+        *used = align16(first_off + sizeof(int32_t) * (size_t)(groups < k ? 2 * (groups + 1) : k + 1));
     }
 }
 
 // The plan's launches (staged groups reading d_stage, already copied), then
 // the closing launch of the convergence checks its ops make.
-hipError_t launch_step(silu_server *s, const StepPlan &p, const char *d_stage)
+hipError_t launch_step(silu_server *s, StepPlan &p, const char *d_stage)
 {
-    const int nops = (int)p.ops.size();
     hipError_t e = hipSuccess;
     for (int g = 0; g < 5 && e == hipSuccess; g++) {
         if (!p.count[g] || p.count[g] > BATCH_ARG_OPS) continue;
         BatchArgs ba;
-        int k = 0, total = 0;
-        for (int i = 0; i < nops; i++) {
-            if (p.prec[(size_t)i] != KINDS[g]) continue;
-            ba.op[k] = p.ops[(size_t)i];
-            ba.first[k++] = total;
-            total += (p.ops[(size_t)i].n + SERVE_RPB - 1) / SERVE_RPB;
-        }
-        ba.first[k] = total;
-        ba.nops = k;
+        ba.groups = group_ops(p, KINDS[g], ba.first);
+        ba.nops = p.count[g];
+        for (int i = 0; i < ba.nops; i++) ba.op[i] = p.ops[(size_t)p.order[(size_t)i]];
+        std::copy(p.start.begin(), p.start.end(), ba.start);
         e = launch_sweep_batch_args(KINDS[g], ba, s->stream);
     }
-    for (int i = 0; i < p.nsg && e == hipSuccess; i++)
-        e = launch_sweep_batch(p.sg[i].kind, (const SweepArgs *)(d_stage + p.sg[i].ops_off),
-                               (const int32_t *)(d_stage + p.sg[i].first_off), p.sg[i].k, p.sg[i].total, s->stream);
+    for (int i = 0; i < p.nsg && e == hipSuccess; i++) {
+        const StagedGroup &G = p.sg[i];
+        const SweepArgs *ops = (const SweepArgs *)(d_stage + G.ops_off);
+        const int32_t *first = (const int32_t *)(d_stage + G.first_off);
+        if (G.groups < G.k)
+            e = launch_sweep_groups(G.kind, ops, first, first + G.groups + 1, G.groups, G.total, s->stream);
+        else
+            e = launch_sweep_batch(G.kind, ops, first, G.k, G.total, s->stream);
+    }
     SolveCheckArgs ca;
     ca.count = 0;
     for (const Request &q0 : s->active) {

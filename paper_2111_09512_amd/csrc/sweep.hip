@@ -1165,6 +1165,103 @@ __device__ __forceinline__ int find_op(const int32_t *first, int nops, int b)
     return lo;
 }
 
+// The rows of one unmasked slice for R ops on the same matrix: its values v and
+// its columns are in registers, each op brings its own vectors.  The loads of
+// all R ops are issued before the first is waited for.
+template <class T, int GG, int R>
+__device__ __forceinline__ void group_rows(const SweepArgs *ops, const typename T::VT (&v)[GG][4],
+                                           const int (&col)[GG][4], int row)
+{
+    using XT = typename T::XT;
+    using RT = typename T::RT;
+    using AT = typename T::AT;
+    XT xv[R][GG][4];
+    RT rhs[R];
+    double aux[R], aux2[R], cf[R];
+    bool on[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const SweepArgs &a = ops[r];
+        on[r] = !(a.sctl && *(const volatile int32_t *)&a.sctl->stop);
+        rhs[r] = (RT)0;
+        aux[r] = aux2[r] = 0.0;
+        cf[r] = 1.0;
+        if (!on[r]) continue;
+        const XT *__restrict__ xin = (const XT *)a.xin;
+#pragma unroll
+        for (int q = 0; q < GG; ++q)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) xv[r][q][k] = xin[col[q][k]];
+        if (a.epi != EPI_SPMV) rhs[r] = ((const RT *)a.rhs)[row];
+        diag_operands(a, row, aux[r], aux2[r], cf[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (!on[r]) continue;
+        AT sum = (AT)0;
+#pragma unroll
+        for (int q = 0; q < GG; ++q)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sum = sum + (AT)v[q][k] * (AT)xv[r][q][k];
+        const AT d = ops[r].epi == EPI_SPMV ? sum : (AT)rhs[r] - sum;
+        epilogue_pre<T>(ops[r], row, d, aux[r], aux2[r], cf[r]);
+    }
+}
+
+template <class T, int GG>
+__device__ __forceinline__ void group_slice(const SweepArgs *ops, int cnt, const SlicedView &s, int p0, int row,
+                                            const int32_t *pt)
+{
+    using VT = typename T::VT;
+    const int lane = (int)threadIdx.x & 63;
+    VT v[GG][4];
+    int col[GG][4];
+#pragma unroll
+    for (int q = 0; q < GG; ++q) {
+        if (sizeof(VT) == 8) {
+            const f64x2 *pv = (const f64x2 *)s.val + (p0 >> 1) + 128 * q + lane;
+            const f64x2 lo2 = pv[0], hi2 = pv[64];
+            v[q][0] = (VT)lo2.x;
+            v[q][1] = (VT)lo2.y;
+            v[q][2] = (VT)hi2.x;
+            v[q][3] = (VT)hi2.y;
+        } else {
+            const f32x4 v4 = ((const f32x4 *)s.val)[(p0 >> 2) + 64 * q + lane];
+            v[q][0] = (VT)v4.x;
+            v[q][1] = (VT)v4.y;
+            v[q][2] = (VT)v4.z;
+            v[q][3] = (VT)v4.w;
+        }
+        const i32x4 o = *(const i32x4 *)(pt + 4 * q);
+        col[q][0] = row + o.x;
+        col[q][1] = row + o.y;
+        col[q][2] = row + o.z;
+        col[q][3] = row + o.w;
+    }
+    int j = 0;
+    constexpr int R = GG == 1 ? 4 : 2;
+    for (; j + R <= cnt; j += R) group_rows<T, GG, R>(ops + j, v, col, row);
+    for (; j < cnt; ++j) group_rows<T, GG, 1>(ops + j, v, col, row);
+}
+
+// One 256-row tile of up to GROUP_OPS ops, no checks, on the same row-pattern
+// copy.
+template <class T>
+__device__ __forceinline__ void batch_group(const SweepArgs *ops, int cnt, int tile)
+{
+    const SlicedView s = *ops[0].sv;
+    const int wave = __builtin_amdgcn_readfirstlane(tile * 4 + ((int)threadIdx.x >> 6));
+    if (wave >= s.nslice) return;
+    const int kf = s.sk[wave], p0 = s.sptr[wave], row = wave * 64 + ((int)threadIdx.x & 63);
+    const int32_t *pt = s.ptab + (int)s.pid[row] * s.kp;
+    if (kf >> 2 == 1) group_slice<T, 1>(ops, cnt, s, p0, row, pt);
+    else if (kf >> 2 == 2) group_slice<T, 2>(ops, cnt, s, p0, row, pt);
+    else
+        for (int j = 0; j < cnt; ++j)
+            if (!(ops[j].sctl && *(const volatile int32_t *)&ops[j].sctl->stop))
+                sliced_wave_pat<T, 2>(ops[j], s, wave, kf, p0, pt);
+}
+
 template <class T>
 __global__ void __launch_bounds__(256) k_sweep_batch(const SweepArgs *__restrict__ ops,
                                                      const int32_t *__restrict__ first, int nops)
@@ -1172,6 +1269,19 @@ __global__ void __launch_bounds__(256) k_sweep_batch(const SweepArgs *__restrict
     const int b = (int)blockIdx.x;
     const int i = find_op(first, nops, b);
     batch_tile<T>(ops[i], b - first[i]);
+}
+
+// The same for groups of ops: group i is the ops [start[i], start[i + 1]).
+template <class T>
+__global__ void __launch_bounds__(256) k_sweep_groups(const SweepArgs *__restrict__ ops,
+                                                      const int32_t *__restrict__ first,
+                                                      const int32_t *__restrict__ start, int groups)
+{
+    const int b = (int)blockIdx.x;
+    const int i = find_op(first, groups, b);
+    const int j = start[i], cnt = start[i + 1] - j;
+    if (cnt == 1) batch_tile<T>(ops[j], b - first[i]);
+    else batch_group<T>(ops + j, cnt, b - first[i]);
 }
 
 // The same with the op table in the kernel arguments, sized for at most CAP
@@ -1207,8 +1317,22 @@ hipError_t go_batch_args(const BatchArgs &b, hipStream_t s)
 }
 
 template <class T>
+__global__ void __launch_bounds__(256) k_sweep_groups_args(BatchArgs ba)
+{
+    const int b = (int)blockIdx.x;
+    const int i = find_op(ba.first, ba.groups, b);
+    const int j = ba.start[i], cnt = ba.start[i + 1] - j;
+    if (cnt == 1) batch_tile<T>(ba.op[j], b - ba.first[i]);
+    else batch_group<T>(ba.op + j, cnt, b - ba.first[i]);
+}
+
+template <class T>
 hipError_t go_batch_args_sized(const BatchArgs &b, hipStream_t s)
 {
+    if (b.groups < b.nops) {
+        hipLaunchKernelGGL((k_sweep_groups_args<T>), dim3(b.first[b.groups]), dim3(256), 0, s, b);
+        return hipGetLastError();
+    }
     if (b.nops <= 2) return go_batch_args<T, 2>(b, s);
     if (b.nops <= 8) return go_batch_args<T, 8>(b, s);
     return go_batch_args<T, BATCH_ARG_OPS>(b, s);
@@ -1631,9 +1755,31 @@ hipError_t launch_sweep_batch(Prec p, const SweepArgs *d_ops, const int32_t *d_f
     return hipGetLastError();
 }
 
+template <class T>
+static hipError_t go_groups(const SweepArgs *d_ops, const int32_t *d_first, const int32_t *d_start, int groups, int total,
+                            hipStream_t s)
+{
+    hipLaunchKernelGGL((k_sweep_groups<T>), dim3(total), dim3(256), 0, s, d_ops, d_first, d_start, groups);
+    return hipGetLastError();
+}
+
+hipError_t launch_sweep_groups(Prec p, const SweepArgs *d_ops, const int32_t *d_first, const int32_t *d_start, int groups,
+                               int total, hipStream_t s)
+{
+    if (groups <= 0 || total <= 0) return hipSuccess;
+    switch (p) {
+    case Prec::F64: return go_groups<TF64>(d_ops, d_first, d_start, groups, total, s);
+    case Prec::MIX_RES: return go_groups<TMixRes>(d_ops, d_first, d_start, groups, total, s);
+    case Prec::MIX_L1: return go_groups<TMixL1>(d_ops, d_first, d_start, groups, total, s);
+    case Prec::MIX_L: return go_groups<TMixL>(d_ops, d_first, d_start, groups, total, s);
+    case Prec::MIX_U: return go_groups<TMixU>(d_ops, d_first, d_start, groups, total, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_sweep_batch_args(Prec p, const BatchArgs &b, hipStream_t s)
 {
-    if (b.nops <= 0 || b.nops > BATCH_ARG_OPS || b.first[b.nops] <= 0) return hipSuccess;
+    if (b.nops <= 0 || b.nops > BATCH_ARG_OPS || b.first[b.groups] <= 0) return hipSuccess;
     switch (p) {
     case Prec::F64: return go_batch_args_sized<TF64>(b, s);
     case Prec::MIX_RES: return go_batch_args_sized<TMixRes>(b, s);
