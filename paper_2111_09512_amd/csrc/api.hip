@@ -1263,6 +1263,7 @@ int build_level_layout(silu_ctx *c, const silu_csr *T, LevelInfo *li)
             s.rows = rows;
             s.pairs = (int32_t)((per + 1) / 2);
             s.start = start[(size_t)l];
+            s.level = l;
             pairs[kind] += (int64_t)s.pairs * (rows < 0 ? 64 : rows);
             int &most = kind == 0 ? li->max_pairs : li->max_far_pairs;
             if (rows > 0) most = std::max(most, (int)s.pairs);

@@ -391,6 +391,7 @@ struct alignas(32) LevelSlice {
     int32_t rows;  // rows (one lane each), or -1: one row over 64 lanes
     int32_t pairs; // entry pairs a lane
     int32_t start; // position that divides near from far (for the fill); near: then row0 modulo LEVEL_RING
+    int32_t level; // its level
 };
 struct LevelView {
     const LevelSlice *slices; // of the near entries

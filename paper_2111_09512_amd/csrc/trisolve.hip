@@ -222,6 +222,12 @@ __global__ void __launch_bounds__(256) k_level_far(LevelView L, int f0, int f1)
     }
 }
 
+// `bytes` from p on as a buffer: loads past them give 0, stores do nothing.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t range(const void *p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void *)p, (short)0, bytes, 0x00020000);
+}
+
 // A near slice's operands in registers: up to KP pairs a lane, with their
 // places in the ring, two to a word.
 template <int KP>
@@ -231,20 +237,31 @@ struct SliceRegs {
     double b, piv;
 };
 
-template <int KP, bool UNIT>
+// FIXED: every slice takes the same number of loads, those past its pairs,
+// lanes or rows out of their buffer's range (nothing is fetched): where the
+// number depends on the slice, the compiler has the wait for one slice's
+// operands wait for those of the slices behind it too.
+template <int KP, bool UNIT, bool FIXED>
 __device__ __forceinline__ void load_slice(const LevelView &L, const LevelSlice &d, int lane, SliceRegs<KP> &g)
 {
-    const int nl = lanes_of(d);
-    const int64_t at = d.off + (lane < nl ? lane : 0);
+    constexpr int NONE = 1 << 28; // a slice's operands are far smaller
+    const int nl = lanes_of(d), words = min(d.pairs, KP) * nl;
+    const auto val = range((const double2 *)L.val + d.off, words * 16);
+    const auto near = range((const unsigned *)L.near + d.off, words * 4);
+    int at_v = lane < nl ? lane * 16 : NONE, at_c = lane < nl ? lane * 4 : NONE;
 #pragma unroll
-    for (int p = 0; p < KP; ++p)
-        if (p < d.pairs) { // the same in the whole wave
-            g.v[p] = ((const double2 *)L.val)[at + (int64_t)p * nl];
-            g.c[p] = ((const unsigned *)L.near)[at + (int64_t)p * nl];
+    for (int p = 0; p < KP; ++p) {
+        if (FIXED || p < d.pairs) {
+            g.v[p] = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(val, at_v, 0, 0));
+            g.c[p] = __builtin_amdgcn_raw_buffer_load_b32(near, at_c, 0, 0);
         }
-    const int row = d.row0 + (lane < d.rows ? lane : 0);
-    g.b = L.b[row];
-    if (!UNIT) g.piv = L.piv[row];
+        at_v += nl * 16;
+        at_c += nl * 4;
+    }
+    const int bytes = (d.rows < 0 ? 1 : d.rows) * 8;
+    g.b = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(range(L.b + d.row0, bytes), lane * 8, 0, 0));
+    if (!UNIT)
+        g.piv = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(range(L.piv + d.row0, bytes), lane * 8, 0, 0));
 }
 
 // Sum of a slice's products, each lane's in ascending order.
@@ -264,6 +281,14 @@ __device__ __forceinline__ double slice_sum(const SliceRegs<KP> &g, const double
         s = s + g.v[p].y * x[2 * p + 1];
     }
     return s;
+}
+
+template <int KP, int P>
+__device__ __forceinline__ double slice_sum_of(int pairs, const SliceRegs<KP> &g, const double *ring)
+{
+    if constexpr (P > 1)
+        if (pairs < P) return slice_sum_of<KP, P - 1>(pairs, g, ring);
+    return slice_sum<KP, P>(g, ring);
 }
 
 // More pairs than registers hold: the others from memory.
@@ -299,27 +324,48 @@ __device__ __forceinline__ void lds_barrier()
 constexpr int RUN_WAVES = 16; // waves of a level run
 constexpr int RUN_DEPTH4 = 2; // slices of up to 4 pairs that each holds (1: 57 GB/s taken in, 2: 70 to 86, 4: 61 to 74)
 
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+
+// A use of v: what loaded it is waited for here.
+__device__ __forceinline__ void arrived(int v) { asm volatile("" ::"v"(v)); }
+
 struct SliceQueue {
-    LevelSlice mine;
+    int64_t off;
+    int row0, level;
+    unsigned shape; // place in the ring, rows, and pairs where they fit
     int next = 64;
     __device__ __forceinline__ LevelSlice pop(const LevelView &L, int q, int end, int lane)
     {
         if (next == 64) {
             const int k = q + RUN_WAVES * lane;
-            mine = L.slices[k < end ? k : end - 1];
+            const LevelSlice s = L.slices[k < end ? k : end - 1];
+            off = s.off;
+            row0 = s.row0;
+            level = s.level;
+            shape = (unsigned)s.start | (unsigned)(s.rows < 0 ? 0 : s.rows) << 16 | (unsigned)min(s.pairs, MANY) << 24;
+            // waits here: behind the branch it would wait for the operands under way whenever a slice is handed out
+            arrived((int)off);
+            arrived(row0);
+            arrived(level);
+            arrived(shape);
             next = 0;
         }
         LevelSlice d;
-        const int lo = __builtin_amdgcn_readlane((int)(uint32_t)mine.off, next),
-                  hi = __builtin_amdgcn_readlane((int)(mine.off >> 32), next);
+        const int lo = __builtin_amdgcn_readlane((int)(uint32_t)off, next),
+                  hi = __builtin_amdgcn_readlane((int)(off >> 32), next);
         d.off = (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-        d.row0 = __builtin_amdgcn_readlane(mine.row0, next);
-        d.rows = __builtin_amdgcn_readlane(mine.rows, next);
-        d.pairs = __builtin_amdgcn_readlane(mine.pairs, next);
-        d.start = __builtin_amdgcn_readlane(mine.start, next);
+        d.row0 = __builtin_amdgcn_readlane(row0, next);
+        d.level = __builtin_amdgcn_readlane(level, next);
+        const unsigned f = (unsigned)__builtin_amdgcn_readlane((int)shape, next);
+        d.start = (int)(f & 0xffff);
+        d.rows = (int)(f >> 16 & 0xff);
+        if (d.rows == 0) d.rows = -1;
+        d.pairs = (int)(f >> 24);
+        if (d.pairs == MANY) d.pairs = L.slices[min(q, end - 1)].pairs;
         ++next;
         return d;
     }
+    static constexpr int MANY = 255;
 };
 
 // Levels [l0, l1) in one workgroup of 16 waves.  The solution of the last
@@ -349,56 +395,40 @@ __global__ void __launch_bounds__(1024) k_level_run(LevelView L, int l0, int l1)
 #pragma unroll
     for (int k = 0; k < DEPTH - 1; ++k) {
         d[k] = queue.pop(L, q + RUN_WAVES * k, end, lane);
-        load_slice<KP, UNIT>(L, d[k], lane, g[k]);
+        load_slice<KP, UNIT, (DEPTH > 1)>(L, d[k], lane, g[k]);
     }
-    int ends = L.first[min(l0 + lane + 1, l1)]; // lane k: the end of level l0 + 64 i + k
-    int to = __builtin_amdgcn_readlane(ends, 0);
-    // the barrier behind a level; false after the last
-    auto next_level = [&]() {
-        lds_barrier();
-        if (++l == l1) return false;
-        const int k = (l - l0) & 63;
-        if (k == 0) ends = L.first[min(l + lane + 1, l1)];
-        to = __builtin_amdgcn_readlane(ends, k);
-        return true;
-    };
-    for (;;) {
+    while (q < end) {
 #pragma unroll
         for (int k = 0; k < DEPTH; ++k) {
             // the slice summed last: its registers take the one DEPTH - 1 behind the next (past the run's
             // end: the last slice, unused)
             constexpr int AHEAD = RUN_WAVES * (DEPTH - 1);
             LevelSlice &dl = d[(k + DEPTH - 1) % DEPTH];
-            if (q >= to && !next_level()) return;
             dl = queue.pop(L, q + AHEAD, end, lane);
-            load_slice<KP, UNIT>(L, dl, lane, g[(k + DEPTH - 1) % DEPTH]);
-            while (q >= to)
-                if (!next_level()) return;
+            if (l < d[k].level) {
+                lds_barrier();
+                ++l;
+            }
+            load_slice<KP, UNIT, (DEPTH > 1)>(L, dl, lane, g[(k + DEPTH - 1) % DEPTH]);
+            for (; l < d[k].level; ++l) lds_barrier();
             double s = 0.0;
-            switch (d[k].pairs) {
-#define SILU_SUM(P) case P: s = P <= KP ? slice_sum<KP, (P <= KP ? P : KP)>(g[k], ring) : slice_sum_long<KP>(L, d[k], g[k], lane, ring); break
-            case 0: break; // no near entries
-                SILU_SUM(1); SILU_SUM(2); SILU_SUM(3); SILU_SUM(4); SILU_SUM(5);
-                SILU_SUM(6); SILU_SUM(7); SILU_SUM(8); SILU_SUM(9); SILU_SUM(10);
-#undef SILU_SUM
-            default: s = slice_sum_long<KP>(L, d[k], g[k], lane, ring); break;
-            }
+            if (d[k].pairs > KP) s = slice_sum_long<KP>(L, d[k], g[k], lane, ring);
+            else if (d[k].pairs > 0) s = slice_sum_of<KP, KP>(d[k].pairs, g[k], ring);
             s = row_sum(d[k], s);
-            if (lane < (d[k].rows < 0 ? 1 : d[k].rows)) {
-                double v = g[k].b - s;
-                if (!UNIT) v = v / g[k].piv;
-                const int place = d[k].start + lane;
-                ring[place < LEVEL_RING ? place : place - LEVEL_RING] = v;
-                L.y[d[k].row0 + lane] = v;
-            }
+            const int rows = d[k].rows < 0 ? 1 : d[k].rows, place = d[k].start + lane;
+            double v = g[k].b - s;
+            if (!UNIT) v = v / g[k].piv;
+            if (lane < rows) ring[place < LEVEL_RING ? place : place - LEVEL_RING] = v;
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), range(L.y + d[k].row0, rows * 8), lane * 8, 0, 0);
             q += RUN_WAVES;
+            if (q >= end) break;
         }
     }
+    for (; l < l1; ++l) lds_barrier();
 }
 
 } // namespace
 
-static_assert(LEVEL_PAIRS <= 10, "k_level_run has bodies for up to 10 pairs");
 static_assert(LEVEL_RING < 65536, "places in the ring are 16-bit");
 
 hipError_t launch_level_reach(int n, int depth, const int32_t *level_ptr, const int32_t *perm, const int32_t *pos,
