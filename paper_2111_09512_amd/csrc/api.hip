@@ -1381,7 +1381,7 @@ int run_levels(silu_ctx *c, const silu_csr *T, LevelInfo *li, int unit, const do
     const int64_t slots = li->near_slots + li->far_slots;
     st = timed_launch(c, 20.0 * (double)slots + 20.0 * (double)n, [&](const char **nm) {
         *nm = "level_pack";
-        return launch_level_pack(slots, (int)n, li->src, (const double *)T->val, li->d_perm, li->dsrc, rhs, li->val, L.b,
+        return launch_level_pack(slots, (int)n, li->src, li->near, li->near_slots, (const double *)T->val, li->d_perm, li->dsrc, rhs, li->val, L.b,
                                  unit ? nullptr : li->vec + 2 * n + 1, c->stream);
     });
     if (st) return st;

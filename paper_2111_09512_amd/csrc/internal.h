@@ -419,7 +419,8 @@ hipError_t launch_level_fill(int nslice, int n, int far_kind, LevelSlice *slices
                              const int32_t *rp, const int32_t *col, void *code, int32_t *src, hipStream_t s);
 hipError_t launch_level_diag(int n, const int32_t *perm, const int32_t *rp, const int32_t *col, int32_t *dsrc,
                              hipStream_t s);
-hipError_t launch_level_pack(int64_t slots, int n, const int32_t *src, const double *val, const int32_t *perm,
+hipError_t launch_level_pack(int64_t slots, int n, const int32_t *src, const uint16_t *near, int64_t near_slots,
+                             const double *val, const int32_t *perm,
                              const int32_t *dsrc, const double *rhs, double *pval, double *pb, double *piv,
                              hipStream_t s);
 hipError_t launch_level_unpack(int n, const int32_t *perm, const double *y, double *out, const double *dinv,
