@@ -1689,11 +1689,17 @@ namespace {
 // call: 7.7 us on 10^3 points, 10 to 14 on 12^3, 19.5 on 16^3.
 //
 // A sequence of calls takes the longer of the two sides: the device with 0.5 us
-// between launches, or the host with 11 us a call and 3 a launch.
+// between launches, or the host with 11 us a call and 3 a launch.  Where the
+// host is ahead (calls on larger matrices before) only the device's side counts,
+// with 0.8 us a launch: a plan that has it busy for longer than the sweeps by
+// themselves is not taken.  What calls in a row gain, a call by itself that is
+// waited for does not: 32^3 points 47.4 us in tiles and 40.8 without, 16^3 40.7
+// and 39.8; with two outer steps 60.9 and 80.6, 54.2 and 79.9.
 struct TileCost {
     int launches = 0;
     double device = 0.0;
     TileCost operator+(const TileCost &o) const { return {launches + o.launches, device + o.device}; }
+    double busy() const { return device + 0.8 * launches; }
     double us(int outer) const { return std::max(11.0 + 3.0 * launches * outer, (device + 0.5 * launches) * outer); }
 };
 double tile_rounds(int64_t rows) { return std::max(1.0, (double)rows / TILE_THREADS); }
@@ -1716,7 +1722,8 @@ struct TilePlan {
 int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed, int outer, int m_L, int m_U, int flags,
                const SweepGeom &gA, const SweepGeom &gL, const SweepGeom &gU, TilePlan *P)
 {
-    constexpr int64_t TILE_MAX_ROWS = 1 << 20; // never of use beyond, by the rates above
+    // beyond, a tile's overlap or its bytes take what it saves (by the rates above 10 % are left at 512^2 points)
+    constexpr int64_t TILE_MAX_ROWS = 1 << 17;
     const int64_t n = A->n_rows;
     const bool diag = gA.kind == SweepKernel::SLICED && gA.slice_code_min < 0 && gL.kind == SweepKernel::SLICED &&
                       gL.slice_code_min < 0 && gU.kind == SweepKernel::SLICED && gU.slice_code_min < 0;
@@ -1815,12 +1822,14 @@ int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed
             }
         }
     }
-    double best = (low[0].cost + up[0].cost).us(outer);
+    const TileCost sweeps = low[0].cost + up[0].cost;
+    double best = sweeps.us(outer);
     for (int l = 0; l < 3; l++)
         for (int u = 0; u < 2; u++) {
             if ((l && !low[l].tiled) || (u && !up[u].tiled)) continue;
-            const double t = (low[l].cost + up[u].cost).us(outer);
-            if (t >= best) continue;
+            const TileCost cost = low[l].cost + up[u].cost;
+            const double t = cost.us(outer);
+            if (t >= best || cost.busy() > 1.05 * sweeps.busy()) continue;
             best = t;
             P->lower = l > 0;
             P->res = l == 2;
@@ -1839,6 +1848,7 @@ int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed
         P->a.buf0 = (int)n;
         P->a.buf1 = (int)(n + words(n));
     }
+    if (!P->whole && !P->lower && !P->upper) return SILU_OK;
     // the sweeps' bytes, as they are credited one by one
     const Prec pL = mixed ? Prec::MIX_L : Prec::F64, pU = mixed ? Prec::MIX_U : Prec::F64;
     auto credit = [&](double *to, Prec p, const silu_csr *N, const Sliced &S, int epi) {

@@ -841,8 +841,12 @@ bool plan_staged(const StepPlan &p)
 // themselves and 43 in groups of up to 8 (1.40 -> 1.12 ms for all their
 // sweeps; in groups of up to 4, 1.14); 40 requests on 3 matrices of up to 48^3
 // points 679, 611 and 594 us in groups of 1, 3 and 4, 621 in groups of 8; 24
-// requests on matrices of up to 32^3 points take 308 us either way.
+// requests on matrices of up to 32^3 points take 308 us either way.  Where few
+// ops have company nothing is gained and the single ones lose (1,280 requests on
+// 64 matrices: 12,930 a second by themselves, 11,900 with groups wherever two
+// ops meet), so groups are made where they save half of a launch's workgroups.
 constexpr int64_t GROUP_TILES = 1536;
+constexpr int64_t GROUP_SAVES = 2;
 int group_ops(StepPlan &p, Prec kind, int32_t *first)
 {
     std::vector<int> &order = p.order;
@@ -857,26 +861,33 @@ int group_ops(StepPlan &p, Prec kind, int32_t *first)
     }
     const int most = (int)std::min<int64_t>(std::max<int64_t>(tiles / GROUP_TILES, 1), GROUP_OPS);
     auto copy = [&](int i) { return p.grouped[(size_t)i] ? p.ops[(size_t)i].sv : nullptr; };
+    // groups first: a group's workgroups run as long as its ops, and would end the launch
     if (most > 1)
         std::stable_sort(order.begin(), order.end(),
-                         [&](int i, int j) { return std::less<const SlicedView *>()(copy(i), copy(j)); });
+                         [&](int i, int j) { return std::less<const SlicedView *>()(copy(j), copy(i)); });
     const int k = (int)order.size();
-    int groups = 0, total = 0;
-    for (int at = 0; at < k;) {
-        const SweepArgs &op = p.ops[(size_t)order[(size_t)at]];
-        int run = 1;
-        if (most > 1 && copy(order[(size_t)at]))
-            while (at + run < k && copy(order[(size_t)(at + run)]) == op.sv) run++;
-        const int parts = (run + most - 1) / most; // of nearly the same size
-        for (int j = 0; j < parts; j++) {
-            first[groups++] = total;
-            start.push_back(at + (int)((int64_t)run * j / parts));
-            total += (op.n + SERVE_RPB - 1) / SERVE_RPB;
+    auto cut = [&](bool share) {
+        int groups = 0, total = 0;
+        start.clear();
+        for (int at = 0; at < k;) {
+            const SweepArgs &op = p.ops[(size_t)order[(size_t)at]];
+            int run = 1;
+            if (share && copy(order[(size_t)at]))
+                while (at + run < k && copy(order[(size_t)(at + run)]) == op.sv) run++;
+            const int parts = (run + most - 1) / most; // of nearly the same size
+            for (int j = 0; j < parts; j++) {
+                first[groups++] = total;
+                start.push_back(at + (int)((int64_t)run * j / parts));
+                total += (op.n + SERVE_RPB - 1) / SERVE_RPB;
+            }
+            at += run;
         }
-        at += run;
-    }
-    first[groups] = total;
-    start.push_back(k);
+        first[groups] = total;
+        start.push_back(k);
+        return groups;
+    };
+    int groups = cut(most > 1);
+    if (groups < k && first[groups] * GROUP_SAVES > tiles) groups = cut(false);
     return groups;
 }
 
