@@ -335,7 +335,7 @@ __device__ __forceinline__ void lds_barrier()
 // are handed out from registers, since a scalar load would have every LDS wait
 // wait for it too.
 constexpr int RUN_WAVES = 16; // waves of a level run
-constexpr int RUN_DEPTH4 = 2; // slices of up to 4 pairs that each holds (1: 57 GB/s taken in, 2: 70 to 86, 4: 61 to 74)
+constexpr int RUN_DEPTH4 = 2; // slices of up to 4 pairs that each holds (1: 57 GB/s taken in, 2: 70 to 86, 3: the same)
 
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
@@ -386,10 +386,15 @@ struct SliceQueue {
 // stream of one: 112 GB/s with 256 KB in flight, 64 GB/s with 128 KB).  A
 // slice's registers are loaded again after it was summed and, unless the wave's
 // next slice is of the same level, after the barrier, so that the loads' issue
-// does not stand between a level and the next (68 against 98 GB/s).  Levels of
-// 437 rows of 20 entries: 0.99 us each, 98 GB/s (a launch each: 4.2 to 5.2 us);
-// of 692 rows of 6 entries 0.82 us, of 350 rows of 3 0.43 us.  Non-temporal
-// loads came to 42 GB/s, touching the factor ahead by four further waves to 55.
+// does not stand between a level and the next (68 against 98 GB/s).  A slice
+// knows its level, so that each wave counts its barriers and meets no branch
+// whose loads would be waited for behind it.  Levels of 692 rows of 6 entries:
+// 0.89 us each (0.96 where every sum waited for all loads in flight; a launch
+// each: 4.3), of which memory is no longer the larger part: holding three
+// slices, or operands that others had brought into the L2, changed nothing.
+// Levels of 437 rows of 20 entries 1.2 us, of 350 rows of 3 0.43 us.
+// Non-temporal loads came to 42 GB/s, touching the factor ahead by four further
+// waves to 55.
 template <int KP, int DEPTH, bool UNIT>
 __global__ void __launch_bounds__(1024) k_level_run(LevelView L, int l0, int l1)
 {
