@@ -1688,22 +1688,25 @@ namespace {
 // 3.0 to 3.6 us up to 48^3.  5/5 steps on 32^3: 14.1/12.8.  One workgroup for the
 // call: 7.7 us on 10^3 points, 10 to 14 on 12^3, 19.5 on 16^3.
 //
-// A sequence of calls takes the longer of the two sides: the device with 0.5 us
-// between launches, or the host with 11 us a call and 3 a launch.  Where the
-// host is ahead (calls on larger matrices before) only the device's side counts,
-// with 0.8 us a launch: a plan that has it busy for longer than the sweeps by
-// themselves is not taken.  What calls in a row gain, a call by itself that is
-// waited for does not: 32^3 points 47.4 us in tiles and 40.8 without, 16^3 40.7
-// and 39.8; with two outer steps 60.9 and 80.6, 54.2 and 79.9.
+// A sequence of calls takes the longer of the two sides: the device, where
+// sweeps that follow one another come to 2.5 us each up to 40^3 points, or the
+// host with 15 us a call and 2.5 a launch.  So what tiles gain falls with the
+// outer steps of a call: 32^3 points 27.5 -> 19.4 us with one, 48.2 -> 45.1 with
+// two of 4/4, but 66.4 to 68.5 us with four, where the sweeps by themselves take
+// 63.7.
+// Where the host is ahead (calls on larger matrices before) only the device's
+// side counts: a plan that has it busy for 1.5 times as long as the sweeps, as on
+// 40^3 points, is not taken.  A call by itself that is waited for gains
+// only from two outer steps on: 32^3 points 47.4 us in tiles and 40.8 without,
+// 16^3 40.7 and 39.8; with two steps 60.9 and 80.6, 54.2 and 79.9.
 struct TileCost {
     int launches = 0;
     double device = 0.0;
     TileCost operator+(const TileCost &o) const { return {launches + o.launches, device + o.device}; }
-    double busy() const { return device + 0.8 * launches; }
-    double us(int outer) const { return std::max(11.0 + 3.0 * launches * outer, (device + 0.5 * launches) * outer); }
+    double us(int outer) const { return std::max(15.0 + 2.5 * launches * outer, device * outer); }
 };
 double tile_rounds(int64_t rows) { return std::max(1.0, (double)rows / TILE_THREADS); }
-TileCost sweep_cost(double bytes) { return {1, std::max(3.5, 2.6 + bytes / 4.5e6)}; }
+TileCost sweep_cost(double bytes) { return {1, std::max(2.5, 1.6 + bytes / 4.5e6)}; }
 TileCost tile_cost(double rounds, double all_bytes) { return {1, 3.2 + 1.1 * rounds + all_bytes / 6e6}; }
 double whole_us(int64_t n, int phases) { return 2.6 + 0.8 * phases * tile_rounds(n); }
 
@@ -1765,7 +1768,7 @@ int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed
     Option low[3] = {{false, resA, a}, {false, {}, a}, {false, {}, a}}, up[2] = {{false, {}, a}, {false, {}, a}};
     for (int k = 2; k <= m_L; k++) low[0].cost = low[0].cost + one_L;
     for (int k = 2; k <= m_U; k++) up[0].cost = up[0].cost + one_U;
-    if (m_L == 1 && m_U == 1) up[0].cost = {1, 3.5}; // the update
+    if (m_L == 1 && m_U == 1) up[0].cost = {1, 2.5}; // the update
     auto better = [](Option &o, const TileCost &cost) {
         if (o.tiled && cost.device >= o.cost.device) return false;
         o.tiled = true;
@@ -1823,13 +1826,17 @@ int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed
         }
     }
     const TileCost sweeps = low[0].cost + up[0].cost;
-    double best = sweeps.us(outer);
+    double best = 0.97 * sweeps.us(outer);
     for (int l = 0; l < 3; l++)
         for (int u = 0; u < 2; u++) {
             if ((l && !low[l].tiled) || (u && !up[u].tiled)) continue;
-            const TileCost cost = low[l].cost + up[u].cost;
+            TileCost cost = low[l].cost + up[u].cost;
+            if (l || u) { // beside tiles a sweep takes 0.9 us more, and a tile 0.4
+                const int tiled = (l > 0) + (u > 0);
+                cost.device += 0.4 * tiled + 0.9 * (cost.launches - tiled);
+            }
             const double t = cost.us(outer);
-            if (t >= best || cost.busy() > 1.05 * sweeps.busy()) continue;
+            if (t >= best || cost.device > 1.5 * sweeps.device) continue;
             best = t;
             P->lower = l > 0;
             P->res = l == 2;
@@ -1837,7 +1844,7 @@ int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed
             P->upper = u > 0;
             P->u = up[u].args;
         }
-    if ((double)(n + 2 * words(n)) <= lds && std::max(11.0 + 3.0, 0.5 + whole_us(n, outer * (m_L + m_U))) < best) {
+    if ((double)(n + 2 * words(n)) <= lds && std::max(15.0 + 2.5, whole_us(n, outer * (m_L + m_U))) < best) {
         P->whole = true;
         P->a = a;
         P->a.tile = (int)n;
