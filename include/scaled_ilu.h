@@ -477,16 +477,23 @@ int silu_nrbe(silu_ctx *ctx, const silu_csr *A, const double *b, const double *x
  * Direct solve T out = rhs by level-set scheduling (Section 4): rows are
  * grouped by the level of the elimination DAG, rows inside a level in
  * parallel; consecutive narrow levels share a launch, a wide one has its own.
- * The first solve lays T's pattern out level by level where that pays (many
- * narrow levels; cached in the context: about 6 bytes an entry, and 8 more for
- * the values that each solve packs into it).
+ * T's pattern is laid out level by level where that pays (many narrow levels)
+ * and cached in the context: 6 bytes for an entry that its run of levels holds
+ * on chip, 8 for one further back, and 8 more for the values that each solve
+ * packs into it, where entries are slots, in pairs, of which padding may make
+ * up to four times the entries; and 28 bytes a row.
  * SILU_NO_GRAPH changes nothing.  T: FP64 CSR, lower (uplo =
  * SILU_LOWER) or upper triangular.  diag = SILU_UNIT: the diagonal is taken
  * as 1 and stored diagonal entries are not read; SILU_NONUNIT: every row must
  * store its diagonal, and the row is divided by it.  rhs, out: FP64 [n],
- * distinct.  The level analysis of T is made on first use (synchronous: the
- * pattern is copied to the host) and cached in the context, keyed by T's
- * pointers and sizes; the solve itself is asynchronous.
+ * distinct.  The level analysis and the layout of T are made by silu_analyze or
+ * on first use (synchronous: the pattern is copied to the host) and cached in
+ * the context, keyed by T's pointers and sizes; the solve itself is
+ * asynchronous.  Solves of one context with the same T wait for each other, on
+ * whatever streams.  A solve that is captured into a graph (recordable once T is
+ * analyzed) takes a launch per level on T's arrays: it shares nothing with other
+ * solves, so its replays may run beside any of them, and its result equals the
+ * eager one up to the rounding of the rows' sums.
  * Errors: ARG, SHAPE, PATTERN (an entry on the wrong side), HIP.
  */
 int trisolve_direct(silu_ctx *ctx, const silu_csr *T, int uplo, int diag, const double *rhs, double *out,

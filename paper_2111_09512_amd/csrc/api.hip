@@ -1325,6 +1325,20 @@ int build_level_layout(silu_ctx *c, const silu_csr *T, LevelInfo *li)
     return e == hipSuccess ? SILU_OK : hip_fail(c, e);
 }
 
+// The layout, made once; where it does not fit memory, solves take a launch per level.
+int level_layout(silu_ctx *c, const silu_csr *T, LevelInfo *li)
+{
+    if (li->tried) return SILU_OK;
+    const int st = build_level_layout(c, T, li);
+    if (st == SILU_OK) return st;
+    free_level_layout(*li); // this solve, or later ones, take a launch per level
+    li->steps.clear();
+    (void)hipGetLastError();
+    if (st != SILU_ERR_HIP || c->last_hip != hipErrorOutOfMemory) return st;
+    c->last_hip = hipSuccess;
+    return SILU_OK;
+}
+
 // out = T^{-1} rhs by levels (out may be null), with the fused s_out = dinv *
 // out and xupd += (dcol) out.  scratch: n doubles for out where it is null.
 int run_levels(silu_ctx *c, const silu_csr *T, LevelInfo *li, int unit, const double *rhs, double *out, double *scratch,
@@ -1332,14 +1346,13 @@ int run_levels(silu_ctx *c, const silu_csr *T, LevelInfo *li, int unit, const do
 {
     const int64_t n = T->n_rows;
     int st;
-    if (!li->tried && (st = build_level_layout(c, T, li))) {
-        free_level_layout(*li); // this solve, or later ones, take a launch per level
-        li->steps.clear();
-        (void)hipGetLastError();
-        if (st != SILU_ERR_HIP || c->last_hip != hipErrorOutOfMemory) return st;
-        c->last_hip = hipSuccess;
-    }
-    if (!li->val) { // a launch per level, on the CSR arrays
+    // A solve that is being captured takes the CSR arrays: what it records may be replayed beside other solves
+    // with T, and the level-ordered copy has room for one solve, whose users only their calls put in order
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
+    const bool captured = capture != hipStreamCaptureStatusNone;
+    if (!captured && (st = level_layout(c, T, li))) return st;
+    if (captured || !li->val) { // a launch per level, on the CSR arrays
         LevelArgs a;
         a.perm = li->d_perm;
         a.rp = T->row_ptr;
@@ -1363,10 +1376,7 @@ int run_levels(silu_ctx *c, const silu_csr *T, LevelInfo *li, int unit, const do
         }
         return SILU_OK;
     }
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
-    if (li->ever_used && li->used_on != c->stream && capture == hipStreamCaptureStatusNone)
-        HIPCHK(c, hipStreamWaitEvent(c->stream, li->used, 0));
+    if (li->ever_used && li->used_on != c->stream) HIPCHK(c, hipStreamWaitEvent(c->stream, li->used, 0));
     LevelView L;
     L.slices = li->slices;
     L.first = li->first;
@@ -1410,11 +1420,9 @@ int run_levels(silu_ctx *c, const silu_csr *T, LevelInfo *li, int unit, const do
                           return launch_level_unpack((int)n, li->d_perm, L.y, out, dinv, s_out, xupd, dcol, c->stream);
                       });
     if (st) return st;
-    if (capture == hipStreamCaptureStatusNone) {
-        HIPCHK(c, hipEventRecord(li->used, c->stream));
-        li->used_on = c->stream;
-        li->ever_used = true;
-    }
+    HIPCHK(c, hipEventRecord(li->used, c->stream));
+    li->used_on = c->stream;
+    li->ever_used = true;
     return SILU_OK;
 }
 
@@ -2841,6 +2849,7 @@ int silu_analyze(silu_ctx *c, const silu_csr *T, int uplo, int32_t *depth, int32
     if (st) return st;
     LevelInfo *li = nullptr;
     if ((st = get_levels(c, T, uplo, &li))) return st;
+    if ((st = level_layout(c, T, li))) return st; // so that solves neither allocate nor wait
     *depth = li->depth;
     if (rows_per_level)
         for (int l = 0; l < li->depth; l++) rows_per_level[l] = li->level_ptr[(size_t)l + 1] - li->level_ptr[(size_t)l];
