@@ -1727,9 +1727,9 @@ struct TilePlan {
     double lower_bytes[2] = {}, res_bytes[2] = {}, upper_bytes[2] = {}; // algorithmic, layout
 };
 
-// Which sweeps of an iterative call go into tile launches: none unless A, L_s
-// and U~_s are swept in diagonal slices (whose copies this makes, as the sweeps
-// would).
+// Which sweeps of an iterative call go into tile launches: none unless what the
+// call sweeps of A, L_s and U~_s is swept in diagonal slices (whose copies this
+// makes, as the sweeps would).
 int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed, int outer, int m_L, int m_U, int flags,
                const SweepGeom &gA, const SweepGeom &gL, const SweepGeom &gU, TilePlan *P)
 {
@@ -1739,17 +1739,30 @@ int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed
     const bool diag = gA.kind == SweepKernel::SLICED && gA.slice_code_min < 0 && gL.kind == SweepKernel::SLICED &&
                       gL.slice_code_min < 0 && gU.kind == SweepKernel::SLICED && gU.slice_code_min < 0;
     if (!diag || F->scaled == 0 || n > TILE_MAX_ROWS || n < 2 || F->Ls.nnz == 0 || F->Us.nnz == 0) return SILU_OK;
-    const int xb = mixed ? 4 : 8, st_min = -1;
-    Sliced *SA = nullptr, *SL = nullptr, *SU = nullptr;
-    int st;
-    if ((st = get_sliced(c, A, A->val, 8, st_min, &SA))) return st;
-    if ((st = get_sliced(c, &F->Ls, mixed ? (const void *)F->Ls_val32 : F->Ls.val, xb, st_min, &SL))) return st;
-    if ((st = get_sliced(c, &F->Us, mixed ? (const void *)F->Us_val32 : F->Us.val, xb, st_min, &SU))) return st;
-    if (!SA->ok || !SL->ok || !SU->ok || SA->v.code != 16 || SL->v.code != 16 || SU->v.code != 16) return SILU_OK;
-    if (SL->v.dhi >= 0 || SU->v.dlo <= 0) return SILU_OK; // not strictly triangular: the sweeps take it as it is
-    const int wL = -SL->v.dlo, wU = SU->v.dhi;
-    const double rowA = 8.0 * SA->v.ndiag, rowL = (double)xb * SL->v.ndiag, rowU = (double)xb * SU->v.ndiag;
+    // the matrices that sweeps of the call read, and no other: a copy is not made for the plan alone
     const bool zero = (flags & SILU_ZERO_GUESS) != 0 && m_L >= 2;
+    const bool useA = !(zero && outer == 1), useL = m_L >= 2, useU = m_U >= 2;
+    const int xb = mixed ? 4 : 8, st_min = -1;
+    static const Sliced none{};
+    const Sliced *SA = &none, *SL = &none, *SU = &none;
+    auto copy = [&](const silu_csr *N, const void *val, int vbytes, const Sliced **to, bool *diagonal) {
+        Sliced *S = nullptr;
+        const int e = get_sliced(c, N, val, vbytes, st_min, &S);
+        if (e) return e;
+        *to = S;
+        *diagonal = S->ok && S->v.code == 16;
+        return SILU_OK;
+    };
+    int st;
+    bool ok = true;
+    if (useA && ((st = copy(A, A->val, 8, &SA, &ok)) || !ok)) return st;
+    if (useL && ((st = copy(&F->Ls, mixed ? (const void *)F->Ls_val32 : F->Ls.val, xb, &SL, &ok)) || !ok)) return st;
+    if (useU && ((st = copy(&F->Us, mixed ? (const void *)F->Us_val32 : F->Us.val, xb, &SU, &ok)) || !ok)) return st;
+    // not strictly triangular: the sweeps take it as it is
+    if ((useL && SL->v.dhi >= 0) || (useU && SU->v.dlo <= 0)) return SILU_OK;
+    const int wL = -SL->v.dlo, wU = SU->v.dhi;
+    const double rowA = useA ? 8.0 * SA->v.ndiag : 8.0 * (double)A->nnz / (double)n;
+    const double rowL = (double)xb * SL->v.ndiag, rowU = (double)xb * SU->v.ndiag;
     TileArgs a{};
     a.n = (int)n;
     a.m_L = m_L;
@@ -1871,7 +1884,7 @@ int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed
         to[0] += sweep_bytes(p, n, N->nnz, epi, false, 4.0) + col;
         to[1] += sliced_sweep_bytes(p, S, n) + epi_bytes(p, n, epi, false) + col;
     };
-    credit(P->res_bytes, Prec::F64, A, *SA, m_L >= 2 ? EPI_STORE : EPI_SCALE);
+    if (useA) credit(P->res_bytes, Prec::F64, A, *SA, m_L >= 2 ? EPI_STORE : EPI_SCALE);
     for (int k = 2; k <= m_L; k++)
         credit(P->lower_bytes, pL, &F->Ls, *SL, k < m_L ? EPI_STORE : (m_U >= 2 ? EPI_SCALE : EPI_SCALE_UPDATE));
     for (int k = 2; k <= m_U; k++) credit(P->upper_bytes, pU, &F->Us, *SU, k < m_U ? EPI_STORE : EPI_UPDATE);
