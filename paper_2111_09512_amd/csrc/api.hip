@@ -1693,20 +1693,24 @@ namespace {
 // 40^3, 12.5/11.0 on 48^3, 13.9/13.0 on 56^3; with the residual in it the L loop
 // takes 7.6 us on 16^3, 9.2 on 24^3, 13.3 on 32^3 and 20.3 on 40^3, against a
 // launch of 3.3 to 3.8 us for the residual by itself; a sweep by itself takes
-// 3.0 to 3.6 us up to 48^3.  5/5 steps on 32^3: 14.1/12.8.  One workgroup for the
-// call: 7.7 us on 10^3 points, 10 to 14 on 12^3, 19.5 on 16^3.
+// 3.0 to 3.6 us up to 48^3, and 2.6 to 2.8 behind another.  5/5 steps on 32^3:
+// 14.1/12.8.  One workgroup for the call, in sweeps and residuals of a round
+// each: 1.3 us each and 3.6 (10^3 points: 11 us for 1 x 3/3, 38 for 4 x 3/3; 12^3:
+// 18 and 58).
 //
-// A sequence of calls takes the longer of the two sides: the device, where
-// sweeps that follow one another come to 2.5 us each up to 40^3 points, or the
-// host with 15 us a call and 2.5 a launch.  So what tiles gain falls with the
-// outer steps of a call: 32^3 points 27.5 -> 19.4 us with one, 48.2 -> 45.1 with
-// two of 4/4, but 66.4 to 68.5 us with four, where the sweeps by themselves take
-// 63.7.
-// Where the host is ahead (calls on larger matrices before) only the device's
-// side counts: a plan that has it busy for 1.5 times as long as the sweeps, as on
-// 40^3 points, is not taken.  A call by itself that is waited for gains
-// only from two outer steps on: 32^3 points 47.4 us in tiles and 40.8 without,
-// 16^3 40.7 and 39.8; with two steps 60.9 and 80.6, 54.2 and 79.9.
+// A sequence of calls takes the longer of the two sides: the device, or the host
+// with 15 us a call and 2.5 a launch, and is what the plan makes short.  Calls
+// elsewhere pay for what tiles keep the device longer: behind work that the host
+// runs ahead of (a finer level), and, with one outer step, a call by itself that
+// is waited for; with two or more such a call gains too, launches being dearer to
+// it.  So a plan is not taken where the device is busy 1.4 times as long as with
+// the sweeps (one workgroup: 1.25 times, where tiles are as good).  Sweeps / tiles,
+// in us, 3/3 steps: in a row, alone, behind a call on 128^3 points:
+//   16^3       27.2/17.9  35.9/36.3  14.6/14.6    32^3       27.1/21.0  37.1/39.8  15.2/18.5
+//   24^3       26.8/17.8  36.6/38.2  14.6/17.6    32^3, two  44.2/33.7  72.0/56.3  31.0/35.6
+// A recorded call costs the host one launch whatever it holds, so its plan is the
+// one that keeps the device shortest (24^3, four steps: a replay 56 us with the
+// sweeps, 63 with the plan of a sequence).
 struct TileCost {
     int launches = 0;
     double device = 0.0;
@@ -1714,9 +1718,10 @@ struct TileCost {
     double us(int outer) const { return std::max(15.0 + 2.5 * launches * outer, device * outer); }
 };
 double tile_rounds(int64_t rows) { return std::max(1.0, (double)rows / TILE_THREADS); }
-TileCost sweep_cost(double bytes) { return {1, std::max(2.5, 1.6 + bytes / 4.5e6)}; }
+TileCost sweep_cost(double bytes) { return {1, std::max(2.65, 1.6 + bytes / 4.5e6)}; }
 TileCost tile_cost(double rounds, double all_bytes) { return {1, 3.2 + 1.1 * rounds + all_bytes / 6e6}; }
-double whole_us(int64_t n, int phases) { return 2.6 + 0.8 * phases * tile_rounds(n); }
+double whole_us(int64_t n, int phases) { return 3.6 + 1.33 * phases * tile_rounds(n); }
+constexpr double TILE_BUSY = 1.4, WHOLE_BUSY = 1.25; // device time in that of the sweeps, at most
 
 struct TilePlan {
     bool whole = false;              // the call in one launch of one workgroup
@@ -1789,7 +1794,7 @@ int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed
     Option low[3] = {{false, resA, a}, {false, {}, a}, {false, {}, a}}, up[2] = {{false, {}, a}, {false, {}, a}};
     for (int k = 2; k <= m_L; k++) low[0].cost = low[0].cost + one_L;
     for (int k = 2; k <= m_U; k++) up[0].cost = up[0].cost + one_U;
-    if (m_L == 1 && m_U == 1) up[0].cost = {1, 2.5}; // the update
+    if (m_L == 1 && m_U == 1) up[0].cost = {1, 2.65}; // the update
     auto better = [](Option &o, const TileCost &cost) {
         if (o.tiled && cost.device >= o.cost.device) return false;
         o.tiled = true;
@@ -1813,7 +1818,7 @@ int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed
                 rounds += tile_rounds(rows);
             }
             for (int res = 0; res < 2 && (double)(rl + nb * words(bl)) <= lds; res++) {
-                const TileCost t = tile_cost(rounds + (res ? 1.5 * tile_rounds(rl) : 0.0),
+                const TileCost t = tile_cost(rounds + (res ? 2.2 * tile_rounds(rl) : 0.0),
                                              tiles * (sweeps + rl * (res ? rowA + 16.0 : 8.0)));
                 Option &o = low[1 + res];
                 if (!better(o, res ? t : resA + t)) continue;
@@ -1847,7 +1852,12 @@ int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed
         }
     }
     const TileCost sweeps = low[0].cost + up[0].cost;
-    double best = 0.97 * sweeps.us(outer);
+    // recorded, by the library or by the caller: a replay costs the host the same whatever it holds
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess) (void)hipGetLastError();
+    const bool recorded = capture != hipStreamCaptureStatusNone;
+    auto span = [&](const TileCost &cost) { return recorded ? cost.device * outer : cost.us(outer); };
+    double best = 0.97 * span(sweeps);
     for (int l = 0; l < 3; l++)
         for (int u = 0; u < 2; u++) {
             if ((l && !low[l].tiled) || (u && !up[u].tiled)) continue;
@@ -1856,8 +1866,8 @@ int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed
                 const int tiled = (l > 0) + (u > 0);
                 cost.device += 0.4 * tiled + 0.9 * (cost.launches - tiled);
             }
-            const double t = cost.us(outer);
-            if (t >= best || cost.device > 1.5 * sweeps.device) continue;
+            const double t = span(cost);
+            if (t >= best || cost.device > TILE_BUSY * sweeps.device) continue;
             best = t;
             P->lower = l > 0;
             P->res = l == 2;
@@ -1865,7 +1875,9 @@ int plan_tiles(silu_ctx *c, const silu_csr *A, const silu_factors *F, bool mixed
             P->upper = u > 0;
             P->u = up[u].args;
         }
-    if ((double)(n + 2 * words(n)) <= lds && std::max(15.0 + 2.5, whole_us(n, outer * (m_L + m_U))) < best) {
+    const TileCost whole{1, whole_us(n, outer * (m_L + m_U))}; // of all outer steps
+    if ((double)(n + 2 * words(n)) <= lds && (recorded ? whole.device : whole.us(1)) < best &&
+        whole.device <= WHOLE_BUSY * outer * sweeps.device) {
         P->whole = true;
         P->a = a;
         P->a.tile = (int)n;
