@@ -1225,7 +1225,9 @@ int build_level_layout(silu_ctx *c, const silu_csr *T, LevelInfo *li)
     };
     for (int l = 0; l < depth; l++) {
         LevelStep *run = li->steps.empty() || li->steps.back().wide ? nullptr : &li->steps.back();
-        const bool wide = level_is_wide(weight[(size_t)l]);
+        // a run's level must fit the ring, whatever the costs say: its rows would overwrite one another's places
+        const bool wide = level_is_wide(weight[(size_t)l]) ||
+                          li->level_ptr[(size_t)l + 1] - li->level_ptr[(size_t)l] > LEVEL_RING;
         if (!wide && run && reach[(size_t)l] < li->level_ptr[(size_t)run->l0]) {
             run->l1 = l + 1;
             run_weight += weight[(size_t)l];
