@@ -102,3 +102,48 @@ def test_recorded_plans(B, hip, N, steps, nodes):
         torch.cuda.synchronize()
         assert torch.isfinite(junk).all()
     assert hip.hipGraphExecDestroy(ex) == 0 and hip.hipGraphDestroy(g) == 0
+
+
+# box, (outer, m_L, m_U), (tile launches, all launches): each form, with a ragged last tile, up to six steps, and a
+# reach larger than the tile (23 x 25: tiles of 256 rows)
+FORMS = {
+    "whole": ((5, 4, 3), (1, 3, 3), (1, 1)),
+    "whole_two": ((5, 4, 3), (2, 1, 3), (1, 1)),
+    "L_with_residual_and_U": ((16, 16, 17), (1, 5, 5), (2, 2)),
+    "L_with_residual_and_U_two": ((30, 9, 40), (2, 3, 4), (4, 4)),
+    "L_with_residual_and_U_unequal": ((20, 20, 21), (1, 4, 6), (2, 2)),
+    "L_with_residual": ((16, 16, 17), (1, 5, 2), (1, 2)),
+    "L_and_U": ((23, 25, 27), (1, 5, 5), (2, 3)),
+    "L_and_U_two": ((23, 25, 27), (2, 6, 6), (4, 6)),
+    "L_and_U_three_steps": ((32, 33, 31), (1, 3, 3), (2, 3)),
+    "L": ((23, 25, 27), (1, 6, 2), (1, 3)),
+    "U": ((36, 35, 37), (1, 3, 3), (1, 4)),
+    "U_after_one": ((16, 16, 17), (2, 1, 3), (2, 4)),
+}
+
+
+@pytest.mark.parametrize("name", list(FORMS))
+def test_forms(orc, B, name):
+    from tests.test_gpu_tile import strip
+
+    shape, (outer, m_L, m_U), want = FORMS[name]
+    say("tile form", name)
+    ctx = B.Context()
+    A = strip(*shape)
+    Ls, U = orc.ilu0(A)
+    d, dinv, Us = orc.scale_rows(U)
+    Ad, Ld, Ud = B.Csr.from_host(A), B.Csr.from_host(Ls), B.Csr.from_host(U)
+    b, x0 = W.rhs(A.n, 1), W.rhs(A.n, 2)
+    bd = dev(b)
+    for F in (ctx.ilu_scale_factors(Ld, Ud, fp32=True), ctx.ilu_scale_factors_rowcol(Ld, Ud, 3, fp32=True)):
+        for mixed in (False, True):
+            for zero in (False, True):
+                start = np.zeros(A.n) if zero else x0
+                got, plain = dev(start), dev(start)
+                seen = launches(ctx, lambda: ctx.ilu_smooth(Ad, F, bd, got, outer, m_L, m_U, mixed=mixed, zero_guess=zero))
+                if not mixed and not zero:
+                    assert seen == want, seen
+                ctx.ilu_smooth(Ad, F, bd, plain, outer, m_L, m_U, mixed=mixed, zero_guess=zero, kernel="rowpat")
+                np.testing.assert_array_equal(host(got), host(plain))
+                if F.scaled == 1 and not mixed:
+                    np.testing.assert_array_equal(host(got), orc.smooth(A, Ls, Us, dinv, b, start, outer, m_L, m_U))
