@@ -32,6 +32,7 @@ __global__ void __launch_bounds__(256) k_scale_rows(int n, const int32_t *__rest
     __shared__ int32_t rp[SCALE_ROWS + 1];
     __shared__ double piv[SCALE_ROWS];
     const int t = (int)threadIdx.x, r0 = (int)blockIdx.x * SCALE_ROWS, nr = min(SCALE_ROWS, n - r0);
+    const int nnz = us_nnz + n; // of U
     if (t < nr) {
         const int i = r0 + t, p0 = Urp[i], p1 = Urp[i + 1];
         rp[t] = p0;
@@ -39,7 +40,7 @@ __global__ void __launch_bounds__(256) k_scale_rows(int n, const int32_t *__rest
         if (i == n - 1) Usrp[n] = p1 - n;
         Usrp[i] = p0 - i;
         double u = 0.0;
-        if (p1 <= p0 || Ucol[p0] != i) {
+        if (p1 <= p0 || p0 < 0 || p1 > nnz || Ucol[p0] != i) {
             atomicMin(&flags[0], i);
         } else {
             u = Uval[p0];
@@ -50,8 +51,9 @@ __global__ void __launch_bounds__(256) k_scale_rows(int n, const int32_t *__rest
         piv[t] = u;
     }
     __syncthreads();
-    const unsigned e1 = (unsigned)rp[nr];
-    for (unsigned eb = (unsigned)(rp[0] + t); eb < e1; eb += 256 * SCALE_PER) {
+    // row pointers that do not ascend or leave the arrays (flagged above) lead to no read outside them
+    const unsigned e1 = (unsigned)min(max(rp[nr], 0), nnz);
+    for (unsigned eb = (unsigned)max(rp[0], 0) + t; eb < e1; eb += 256 * SCALE_PER) {
         int j[SCALE_PER];
         double uv[SCALE_PER];
 #pragma unroll
