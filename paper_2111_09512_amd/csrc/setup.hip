@@ -14,11 +14,18 @@ namespace {
 //           an entry left of it); flags[1]: first row with a zero or
 //           non-finite pivot.  Both start at INT32_MAX.
 //
-// A workgroup takes 256 rows: one lane a row reads the row's range and pivot
-// into LDS, then all lanes stream the rows' entries, each finding its row by a
-// binary search of the 257 row pointers in LDS.  Entries are read and written
-// in order.  20-entry rows, n = 1M (564 MB moved): 1,196 us with one lane a
+// k_scale_rows: a workgroup takes 256 rows.  One lane a row reads the row's
+// range and pivot into LDS, then all lanes stream the rows' entries, each
+// finding its row by a binary search of the 257 row pointers in LDS.  Entries
+// are read and written in order.  20-entry rows, n = 1M (564 MB moved): 1,196 us with one lane a
 // row, a cache line a lane and array; 155 us so, 3.6 TB/s.
+//
+// k_scale_rows_short, one lane a row: where the entries are few, the chain of
+// one row is what a launch takes, and the code that the other form has to fetch
+// is longer.  Short / streamed, us, by U's entries: 6,480 3.6/5.3, 91,656
+// 5.6/7.6, 382,996 4.8/6.4, 502,866 8.0/9.0, 541,678 (20 a row) 21.0/19.0,
+// 852,650 13.6/9.7, 1,973,466 50/15.  So it takes up to SCALE_SHORT of them.
+constexpr int SCALE_SHORT = 1 << 19, SCALE_LONG = 64;
 constexpr int SCALE_ROWS = 256;
 constexpr int SCALE_PER = 4; // entries a lane has in flight
 __global__ void __launch_bounds__(256) k_scale_rows(int n, const int32_t *__restrict__ Urp,
@@ -87,6 +94,53 @@ __global__ void __launch_bounds__(256) k_scale_rows(int n, const int32_t *__rest
             Usval[o] = v;
             if (Us32) Us32[o] = (float)v;
         }
+    }
+}
+
+__global__ void __launch_bounds__(256) k_scale_rows_short(int n, const int32_t *__restrict__ Urp,
+                                                          const int32_t *__restrict__ Ucol,
+                                                          const double *__restrict__ Uval, int32_t *__restrict__ Usrp,
+                                                          int32_t *__restrict__ Uscol, double *__restrict__ Usval,
+                                                          double *__restrict__ d, double *__restrict__ dinv,
+                                                          float *__restrict__ Us32, int noscale, int32_t us_nnz,
+                                                          int32_t *flags)
+{
+    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    int p0 = 0, p1 = 0; // the entries of this lane's row (none unless it is well formed)
+    double u = 0.0;
+    if (i < n) {
+        const int q0 = Urp[i], q1 = Urp[i + 1];
+        if (i == n - 1) Usrp[n] = q1 - n;
+        Usrp[i] = q0 - i;
+        if (q1 <= q0 || q0 < 0 || q1 > us_nnz + n || Ucol[q0] != i) {
+            atomicMin(&flags[0], i);
+        } else {
+            u = Uval[q0];
+            if (!(u != 0.0) || !isfinite(u)) atomicMin(&flags[1], i);
+            d[i] = u;
+            dinv[i] = 1.0 / u;
+            p0 = q0;
+            p1 = q1;
+        }
+    }
+    auto scale = [&](int row, double piv, int p, int end, int step) {
+        for (; p < end; p += step) {
+            const int j = Ucol[p], o = p - row - 1; // bounded as above
+            const bool in = o >= 0 && o < us_nnz;
+            if (j <= row || !in) atomicMin(&flags[0], row);
+            if (!in) continue;
+            const double v = noscale ? Uval[p] : Uval[p] / piv;
+            Uscol[o] = j;
+            Usval[o] = v;
+            if (Us32) Us32[o] = (float)v;
+        }
+    };
+    // rows far longer than their neighbours are shared by the wave
+    const bool shared = p1 - p0 > SCALE_LONG;
+    if (!shared) scale(i, u, p0 + 1, p1, 1);
+    for (unsigned long long m = __ballot(shared); m; m &= m - 1) {
+        const int k = (int)__ffsll(m) - 1, lane = (int)threadIdx.x & 63;
+        scale(__shfl(i, k), __shfl(u, k), __shfl(p0, k) + 1 + lane, __shfl(p1, k), 64);
     }
 }
 
@@ -624,8 +678,13 @@ hipError_t launch_scale_rows(int n, const int32_t *Urp, const int32_t *Ucol, con
                              int32_t us_nnz, int32_t *flags, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_scale_rows, dim3(blocks_for(n, SCALE_ROWS)), dim3(256), 0, s, n, Urp, Ucol, Uval, Usrp, Uscol,
-                       Usval, d, dinv, Us32, noscale, us_nnz, flags);
+    const dim3 g(blocks_for(n, SCALE_ROWS)), b(256);
+    if (us_nnz + n <= SCALE_SHORT)
+        hipLaunchKernelGGL(k_scale_rows_short, g, b, 0, s, n, Urp, Ucol, Uval, Usrp, Uscol, Usval, d, dinv, Us32, noscale,
+                           us_nnz, flags);
+    else
+        hipLaunchKernelGGL(k_scale_rows, g, b, 0, s, n, Urp, Ucol, Uval, Usrp, Uscol, Usval, d, dinv, Us32, noscale,
+                           us_nnz, flags);
     return hipGetLastError();
 }
 
