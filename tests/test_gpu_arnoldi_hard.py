@@ -87,3 +87,18 @@ def test_stalling_restarts(orc, B, restart):
     assert k == k_ref == 120
     np.testing.assert_allclose(h, h_ref, rtol=1e-6)
     assert abs(got - ref) <= 1e-6 * ref
+
+
+def test_no_direction_behind_the_last_step(B):
+    """A solve that stops after its first step applies the preconditioner once."""
+    say("arnoldi one step")
+    A = W.poisson7(20)
+    L, U = B.factor_iluk(A, 0)
+    ctx = B.Context()
+    F = ctx.ilu_scale_factors(B.Csr.from_host(L), B.Csr.from_host(U))
+    Ad, b, x = B.Csr.from_host(A), dev(W.rhs(A.n, 1)), dev(np.zeros(A.n))
+    ctx.set_timing(True)
+    k, _ = ctx.fgmres(Ad, F, b, x, restart=30, max_iters=60, tol=0.5, m_L=3, m_U=3, kernel="rowpat")
+    sweeps = sum(v["launches"] for name, v in ctx.stats().items() if name.startswith("sweep"))
+    assert k == 1
+    assert sweeps == 1 + 4 + 1  # the first residual, one smoother call from zero, the product with A
