@@ -53,9 +53,8 @@ struct LevelInfo {
     int64_t near_slots = 0, far_slots = 0;
     int max_pairs = 0, max_far_pairs = 0; // of a lane, in slices of a row a lane
     std::vector<LevelStep> steps;
-    // the last solve that used that room: one on another stream waits for it
+    // the last solve that used that room: the next one, on whatever stream, waits for it
     hipEvent_t used = nullptr;
-    hipStream_t used_on = nullptr;
     bool ever_used = false;
 };
 
@@ -1378,7 +1377,8 @@ int run_levels(silu_ctx *c, const silu_csr *T, LevelInfo *li, int unit, const do
         }
         return SILU_OK;
     }
-    if (li->ever_used && li->used_on != c->stream) HIPCHK(c, hipStreamWaitEvent(c->stream, li->used, 0));
+    // (also on what looks like the same stream: a handle may be that of a stream made since)
+    if (li->ever_used) HIPCHK(c, hipStreamWaitEvent(c->stream, li->used, 0));
     LevelView L;
     L.slices = li->slices;
     L.first = li->first;
@@ -1423,7 +1423,6 @@ int run_levels(silu_ctx *c, const silu_csr *T, LevelInfo *li, int unit, const do
                       });
     if (st) return st;
     HIPCHK(c, hipEventRecord(li->used, c->stream));
-    li->used_on = c->stream;
     li->ever_used = true;
     return SILU_OK;
 }
