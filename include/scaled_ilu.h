@@ -244,10 +244,9 @@ int ilu_scale_factors_rowcol(silu_ctx *ctx, const silu_csr *L, const silu_csr *U
  * a synchronous scan of x (returns NONFINITE); SILU_VALIDATE checks the CSR
  * structures first.  With F->scaled == 0 (SILU_NO_SCALING) the U loop is the
  * unscaled Richardson iteration z <- y - (U - I) z (FP64 only).
- * SILU_GRAPH (iterative form; ignored with SILU_DIRECT, whose level sweeps
- * are captured anyway): the first call with a given set of arguments (the
- * matrices' and vectors' pointers, sizes, counts and flags) runs as usual and
- * then records its whole launch sequence into a hipGraph kept in the context;
+ * SILU_GRAPH (iterative form; ignored with SILU_DIRECT): the first call with a
+ * given set of arguments (the matrices' and vectors' pointers, sizes, counts
+ * and flags) runs as usual and then records its whole launch sequence into a hipGraph kept in the context;
  * later calls with the same arguments replay it with one launch, on the same
  * data layouts, with the same results bit for bit.  The graph bakes in the
  * pointers: the caller keeps b, x and ws at those addresses, and any
@@ -414,9 +413,11 @@ int silu_ilu0_fixed_point(silu_ctx *ctx, const silu_csr *A, int sweeps, silu_csr
  * dot products then sum in the relabeled order), the kernel choices,
  * SILU_VALIDATE; SILU_GRAPH is ignored.  ws: at least
  * silu_fgmres_workspace_size(ctx, n, restart, flags) bytes (2 restart + 6
- * n-vectors, 2 more with SILU_REORDER, and a few KB), 256-byte aligned; the context keeps the products of the
- * basis besides (restart^2 doubles and at most 2,048 restart more), made on the first solve.  Synchronous (the small
- * least-squares problem is solved on the host every step).  Errors: ARG,
+ * n-vectors, 2 more with SILU_REORDER, and a few KB), 256-byte aligned; the
+ * context keeps the products of the basis besides, made on the first solve
+ * (with r = min(restart, max_iters): r^2 + 2 r doubles and at most 2,048 r more
+ * on the device, and r + 1 pinned ones, 5 r + 1 with a norm_a).  Synchronous
+ * (the small least-squares problem is solved on the host every step).  Errors: ARG,
  * SHAPE, NOMEM, UNSUPPORTED (factors neither row- nor row/column-scaled),
  * and those of ilu_smooth.
  */
@@ -512,14 +513,14 @@ int trisolve_direct(silu_ctx *ctx, const silu_csr *T, int uplo, int diag, const 
 int trisolve_iter(silu_ctx *ctx, const silu_csr *T, const double *dinv, const double *rhs, double *out, int m,
                   int flags, void *ws, size_t ws_bytes);
 
-/* Level analysis of T (made now if not cached): number of levels in
+/* Level analysis and layout of T (made now if not cached): number of levels in
  * *depth and, if rows_per_level is non-NULL, the row count of every level
  * (host array of at least *depth entries; call once with NULL to size it).
  * Synchronous. */
 int silu_analyze(silu_ctx *ctx, const silu_csr *T, int uplo, int32_t *depth, int32_t *rows_per_level);
 
 /* Drop everything the context cached for the matrix whose row_ptr or
- * col_idx is given (level sets and their graphs, row-block partitions,
+ * col_idx is given (level sets and their layouts, row-block partitions,
  * 16-bit codes, sliced copies).  The caches are keyed by pointers and sizes,
  * so call this before freeing a matrix, or changing its pattern or (for the
  * sliced copies) its values in place.  Synchronizes the context stream. */

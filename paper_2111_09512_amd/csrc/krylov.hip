@@ -19,8 +19,8 @@
 // with w and v_j in one pass over V (k_dots), the sums and the substitution
 // (k_project), w -= V h with the partial sums of w . w in a second pass
 // (k_subtract), and v_{j+1} = w / ||w|| (k_normalize).  48^3 Poisson operator,
-// FGMRES(30) to 1e-8 in 96 steps: 18.7 to 21.6 ms with one vector at a time, 6.7
-// ms so, 4.3 ms with the next direction enqueued before the wait.
+// FGMRES(30) to 1e-8 in 96 or 97 steps: 18.7 to 21.6 ms with one vector at a time,
+// 6.7 ms so, 4.2 to 4.6 ms with the next direction enqueued before the wait.
 #include <algorithm>
 
 #include "internal.h"
