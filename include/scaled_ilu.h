@@ -62,7 +62,7 @@ extern "C" {
 #define SILU_KERNEL_STREAM 0x100  /* CSR-stream sweep kernel (instead of the sliced default)   */
 #define SILU_KERNEL_VECTOR 0x200  /* vector-CSR (lanes-per-row) sweep kernel                */
 #define SILU_KERNEL_BLOCKED 0x400 /* CSR-stream over a row-block partition                  */
-#define SILU_NO_GRAPH 0x800       /* accepted; level-scheduled solves always launch plainly   */
+#define SILU_NO_GRAPH 0x800       /* level-scheduled solves: plain launches, no hipGraph     */
 #define SILU_INDEX32 0x1000       /* sweeps read the 32-bit col_idx, never 16-bit codes      */
 #define SILU_NO_WINDOW 0x2000     /* sweeps never stage the iterate window in LDS            */
 #define SILU_WINDOW 0x4000        /* sweeps stage the window wherever it fits                */
@@ -483,18 +483,21 @@ int silu_nrbe(silu_ctx *ctx, const silu_csr *A, const double *b, const double *x
  * on chip, 8 for one further back, and 8 more for the values that each solve
  * packs into it, where entries are slots, in pairs, of which padding may make
  * up to four times the entries; and 28 bytes a row.
- * SILU_NO_GRAPH changes nothing.  T: FP64 CSR, lower (uplo =
- * SILU_LOWER) or upper triangular.  diag = SILU_UNIT: the diagonal is taken
- * as 1 and stored diagonal entries are not read; SILU_NONUNIT: every row must
- * store its diagonal, and the row is divided by it.  rhs, out: FP64 [n],
- * distinct.  The level analysis and the layout of T are made by silu_analyze or
- * on first use (synchronous: the pattern is copied to the host) and cached in
- * the context, keyed by T's pointers and sizes; the solve itself is
- * asynchronous.  Solves of one context with the same T wait for each other, on
- * whatever streams.  A solve that is captured into a graph (recordable once T is
- * analyzed) takes a launch per level on T's arrays: it shares nothing with other
- * solves, so its replays may run beside any of them, and its result equals the
- * eager one up to the rounding of the rows' sums.
+ * Where it does not pay (few levels, or wide ones) each level is a launch on
+ * T's arrays; a sequence that comes again with the same pointers is captured
+ * into a hipGraph (cached in the context) and replayed; SILU_NO_GRAPH launches
+ * the levels one by one.  T: FP64 CSR, lower (uplo = SILU_LOWER) or upper
+ * triangular.  diag = SILU_UNIT: the diagonal is taken as 1 and stored diagonal
+ * entries are not read; SILU_NONUNIT: every row must store its diagonal, and the
+ * row is divided by it.  rhs, out: FP64 [n], distinct.  The level analysis and
+ * the layout of T are made by silu_analyze or on first use (synchronous: the
+ * pattern is copied to the host) and cached in the context, keyed by T's
+ * pointers and sizes; the solve itself is asynchronous.  Solves of one context
+ * on one layout wait for each other, on whatever streams.  A solve that is
+ * captured into a graph of the caller's (recordable once T is analyzed) takes a
+ * launch per level on T's arrays: it shares nothing with other solves, so its
+ * replays may run beside any of them, and its result equals the eager one up to
+ * the rounding of the rows' sums.
  * Errors: ARG, SHAPE, PATTERN (an entry on the wrong side), HIP.
  */
 int trisolve_direct(silu_ctx *ctx, const silu_csr *T, int uplo, int diag, const double *rhs, double *out,

@@ -176,6 +176,11 @@ void free_compressed(Compressed &C)
     C.wo = nullptr;
 }
 
+// A captured sequence of per-level launches, by what its launches are given (null: seen once, not captured yet).
+using GraphKey = std::tuple<const void *, const void *, const void *, const void *, const void *, const void *,
+                            const void *, const void *, const void *, const void *, int>;
+constexpr size_t LEVEL_GRAPHS = 64; // of a context
+
 struct Pending {
     int kid;
     hipEvent_t e0, e1;
@@ -203,6 +208,7 @@ struct silu_ctx {
     std::map<PartKey, Partition> parts;
     std::map<CompKey, Compressed> comp;
     std::map<SlicedKey, Sliced> sliced;
+    std::map<GraphKey, hipGraphExec_t> graphs;
     std::map<SmoothKey, SmoothGraph> smooth_graphs;
     std::map<ReorderKey, Reorder> reorders;
     hipStream_t capture_stream = nullptr; // private, default priority, for graph capture
@@ -1340,10 +1346,45 @@ int level_layout(silu_ctx *c, const silu_csr *T, LevelInfo *li)
     return SILU_OK;
 }
 
+// The per-level launches as a graph (*ex), captured when the same ones come a second time: where they are few
+// and wide, the launches by themselves are as slow as the levels (25 levels of 2,560 rows: 66 us replayed, 74
+// launched; waited for, 78 and 108).  Null for those that come once, and beyond LEVEL_GRAPHS of them.
+int level_graph(silu_ctx *c, const LevelArgs &a, const LevelInfo *li, int unit, hipGraphExec_t *ex)
+{
+    const GraphKey key{li, a.rp, a.col, a.val, a.rhs, a.out, a.dinv, a.s_out, a.xupd, a.dcol, unit};
+    auto it = c->graphs.find(key);
+    if (it == c->graphs.end()) {
+        if (c->graphs.size() >= LEVEL_GRAPHS) // those seen once make room
+            for (auto g = c->graphs.begin(); g != c->graphs.end();) g = g->second ? std::next(g) : c->graphs.erase(g);
+        if (c->graphs.size() < LEVEL_GRAPHS) c->graphs.emplace(key, nullptr);
+        return SILU_OK;
+    }
+    if (!it->second) {
+        if (!c->capture_stream) HIPCHK(c, hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking));
+        HIPCHK(c, hipStreamBeginCapture(c->capture_stream, hipStreamCaptureModeThreadLocal));
+        hipError_t e = hipSuccess;
+        for (int l = 0; l < li->depth && e == hipSuccess; l++) {
+            const int first = li->level_ptr[(size_t)l], count = li->level_ptr[(size_t)l + 1] - first;
+            e = launch_level(a, unit, li->lanes, first, count, c->capture_stream, nullptr);
+        }
+        hipGraph_t g = nullptr;
+        const hipError_t e2 = hipStreamEndCapture(c->capture_stream, &g);
+        if (e == hipSuccess) e = e2;
+        if (e == hipSuccess) e = hipGraphInstantiate(&it->second, g, nullptr, nullptr, 0);
+        if (g) (void)hipGraphDestroy(g);
+        if (e != hipSuccess) {
+            it->second = nullptr;
+            return hip_fail(c, e);
+        }
+    }
+    *ex = it->second;
+    return SILU_OK;
+}
+
 // out = T^{-1} rhs by levels (out may be null), with the fused s_out = dinv *
 // out and xupd += (dcol) out.  scratch: n doubles for out where it is null.
 int run_levels(silu_ctx *c, const silu_csr *T, LevelInfo *li, int unit, const double *rhs, double *out, double *scratch,
-               const double *dinv, double *s_out, double *xupd, const double *dcol = nullptr)
+               const double *dinv, double *s_out, double *xupd, bool graph, const double *dcol = nullptr)
 {
     const int64_t n = T->n_rows;
     int st;
@@ -1365,12 +1406,24 @@ int run_levels(silu_ctx *c, const silu_csr *T, LevelInfo *li, int unit, const do
         a.s_out = s_out;
         a.xupd = xupd;
         a.dcol = dcol;
+        auto level_bytes = [&](int l) {
+            const int count = li->level_ptr[(size_t)l + 1] - li->level_ptr[(size_t)l];
+            return count * (4.0 + 8.0 + 8.0 + 8.0 + 8.0 + (s_out ? 16.0 : 0.0) + (xupd ? (dcol ? 24.0 : 16.0) : 0.0)) +
+                   12.0 * (double)li->level_nnz[(size_t)l];
+        };
+        hipGraphExec_t ex = nullptr;
+        if (graph && !captured && li->depth > 1 && (st = level_graph(c, a, li, unit, &ex))) return st;
+        if (ex) {
+            double bytes = 0.0;
+            for (int l = 0; l < li->depth; l++) bytes += level_bytes(l);
+            return timed_launch(c, bytes, [&](const char **nm) {
+                *nm = "level_graph";
+                return hipGraphLaunch(ex, c->stream);
+            });
+        }
         for (int l = 0; l < li->depth; l++) {
             const int first = li->level_ptr[(size_t)l], count = li->level_ptr[(size_t)l + 1] - first;
-            double bytes = count * (4.0 + 8.0 + 8.0 + 8.0 + 8.0) + 12.0 * (double)li->level_nnz[(size_t)l];
-            if (s_out) bytes += count * 16.0;
-            if (xupd) bytes += count * (dcol ? 24.0 : 16.0);
-            st = timed_launch(c, bytes, [&](const char **nm) {
+            st = timed_launch(c, level_bytes(l), [&](const char **nm) {
                 return launch_level(a, unit, li->lanes, first, count, c->stream, nm);
             });
             if (st) return st;
@@ -1530,6 +1583,8 @@ int silu_destroy(silu_ctx *c)
     for (auto &kv : c->parts) (void)hipFree(kv.second.d_blk);
     for (auto &kv : c->comp) free_compressed(kv.second);
     for (auto &kv : c->sliced) free_sliced(kv.second);
+    for (auto &kv : c->graphs)
+        if (kv.second) (void)hipGraphExecDestroy(kv.second);
     for (auto &kv : c->smooth_graphs)
         if (kv.second.ex) (void)hipGraphExecDestroy(kv.second.ex);
     for (auto &kv : c->reorders) free_reorder(kv.second);
@@ -2003,11 +2058,12 @@ static int smooth_plain(silu_ctx *c, const silu_csr *A, const silu_factors *F, c
             if ((st = get_levels(c, &F->Ls, SILU_LOWER, &lL))) return st;
             if ((st = get_levels(c, &F->Us, SILU_UPPER, &lU))) return st;
             if ((st = sweep(c, Prec::F64, gA, A, A->val, x, b, EPI_STORE, r, nullptr, nullptr, nullptr))) return st;
+            const bool graph = !(flags & SILU_NO_GRAPH);
             if ((st = run_levels(c, &F->Ls, lL, 1, (const double *)r, nullptr, (double *)tmp[0], F->dinv,
-                                 (double *)s, nullptr)))
+                                 (double *)s, nullptr, graph)))
                 return st;
             if ((st = run_levels(c, &F->Us, lU, 1, (const double *)s, nullptr, (double *)tmp[1], nullptr, nullptr,
-                                 x, dcol)))
+                                 x, graph, dcol)))
                 return st;
             continue;
         }
@@ -2837,7 +2893,8 @@ int trisolve_direct(silu_ctx *c, const silu_csr *T, int uplo, int diag, const do
     }
     LevelInfo *li = nullptr;
     if ((st = get_levels(c, T, uplo, &li))) return st;
-    return run_levels(c, T, li, diag == SILU_UNIT ? 1 : 0, rhs, out, nullptr, nullptr, nullptr, nullptr);
+    return run_levels(c, T, li, diag == SILU_UNIT ? 1 : 0, rhs, out, nullptr, nullptr, nullptr, nullptr,
+                      !(flags & SILU_NO_GRAPH));
 }
 
 int trisolve_iter(silu_ctx *c, const silu_csr *T, const double *dinv, const double *rhs, double *out, int m,
@@ -2915,6 +2972,15 @@ int silu_release(silu_ctx *c, const void *row_ptr, const void *col_idx)
     }
     for (auto it = c->levels.begin(); it != c->levels.end();) {
         if (std::get<0>(it->first) == row_ptr || std::get<1>(it->first) == col_idx) {
+            const LevelInfo *li = &it->second;
+            for (auto g = c->graphs.begin(); g != c->graphs.end();) {
+                if (std::get<0>(g->first) == li) {
+                    if (g->second) (void)hipGraphExecDestroy(g->second);
+                    g = c->graphs.erase(g);
+                } else {
+                    ++g;
+                }
+            }
             free_levels(it->second);
             it = c->levels.erase(it);
         } else {
