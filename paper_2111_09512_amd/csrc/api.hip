@@ -14,6 +14,7 @@
 #include <cmath>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <unordered_map>
 #include <new>
@@ -42,7 +43,7 @@ struct LevelInfo {
     std::vector<int64_t> level_nnz; // off-diagonal entries per level, host
     int depth = 0;
     int lanes = 1;                  // lanes per row of the per-level kernel
-    std::vector<int32_t> perm;      // d_perm on the host, until the first solve
+    std::unique_ptr<int32_t[]> pos; // position of each row, until the layout is made
     // the level-ordered copy, made by the first solve where it pays: its structure, and room for one
     // solve's values (near ones, then far ones) and vectors (right-hand side, solution and a 0, pivots)
     bool tried = false;
@@ -1108,18 +1109,22 @@ int get_levels(silu_ctx *c, const silu_csr *T, int uplo, LevelInfo **out)
         return SILU_OK;
     }
     const int64_t n = T->n_rows;
-    std::vector<int32_t> rp((size_t)n + 1), col((size_t)std::max<int64_t>(T->nnz, 1));
-    HIPCHK(c, hipMemcpyAsync(rp.data(), T->row_ptr, rp.size() * 4, hipMemcpyDeviceToHost, c->stream));
-    if (T->nnz) HIPCHK(c, hipMemcpyAsync(col.data(), T->col_idx, (size_t)T->nnz * 4, hipMemcpyDeviceToHost, c->stream));
+    // (not vectors: clearing them takes as long as the copies)
+    std::unique_ptr<int32_t[]> rp(new int32_t[(size_t)n + 1]), col(new int32_t[(size_t)std::max<int64_t>(T->nnz, 1)]);
+    std::unique_ptr<int32_t[]> lev(new int32_t[(size_t)n]), perm(new int32_t[(size_t)n]);
+    HIPCHK(c, hipMemcpyAsync(rp.get(), T->row_ptr, ((size_t)n + 1) * 4, hipMemcpyDeviceToHost, c->stream));
+    if (T->nnz) HIPCHK(c, hipMemcpyAsync(col.get(), T->col_idx, (size_t)T->nnz * 4, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    std::vector<int32_t> lev((size_t)n, 0);
-    int32_t depth = 0;
+    LevelInfo info;
     for (int64_t s = 0; s < n; s++) {
         const int64_t i = uplo == SILU_LOWER ? s : n - 1 - s;
-        int32_t l = 0;
+        int32_t l = 0, diag = 0;
         for (int32_t p = rp[(size_t)i]; p < rp[(size_t)i + 1]; p++) {
             const int32_t j = col[(size_t)p];
-            if (j == i) continue;
+            if (j == i) {
+                diag++;
+                continue;
+            }
             if (j < 0 || j >= n || (uplo == SILU_LOWER ? j > i : j < i)) {
                 c->bad_row = i;
                 return SILU_ERR_PATTERN;
@@ -1127,34 +1132,41 @@ int get_levels(silu_ctx *c, const silu_csr *T, int uplo, LevelInfo **out)
             l = std::max(l, lev[(size_t)j] + 1);
         }
         lev[(size_t)i] = l;
-        depth = std::max(depth, l + 1);
+        if (l == info.depth) { // a row is at most one level behind the deepest so far
+            info.depth++;
+            info.level_ptr.push_back(0);
+            info.level_nnz.push_back(0);
+        }
+        info.level_ptr[(size_t)l]++; // rows of the level, for now
+        info.level_nnz[(size_t)l] += std::max(rp[(size_t)i + 1] - rp[(size_t)i], 0) - diag;
     }
-    LevelInfo info;
-    info.depth = depth;
-    info.level_ptr.assign((size_t)depth + 1, 0);
-    info.level_nnz.assign((size_t)depth, 0);
-    for (int64_t i = 0; i < n; i++) {
-        info.level_ptr[(size_t)lev[(size_t)i] + 1]++;
-        int64_t off = 0;
-        for (int32_t p = rp[(size_t)i]; p < rp[(size_t)i + 1]; p++) off += col[(size_t)p] != i;
-        info.level_nnz[(size_t)lev[(size_t)i]] += off;
+    const int32_t depth = info.depth;
+    info.level_ptr.push_back(0);
+    std::vector<int32_t> fill((size_t)depth);
+    for (int32_t l = 0, at = 0; l <= depth; l++) {
+        const int32_t rows = info.level_ptr[(size_t)l];
+        info.level_ptr[(size_t)l] = at;
+        if (l < depth) fill[(size_t)l] = at;
+        at += rows;
     }
-    for (int32_t l = 0; l < depth; l++) info.level_ptr[(size_t)l + 1] += info.level_ptr[(size_t)l];
     {
         int64_t off = 0;
         for (int32_t l = 0; l < depth; l++) off += info.level_nnz[(size_t)l];
         const double mean = n > 0 ? (double)off / (double)n : 0.0;
         info.lanes = mean <= 2.0 ? 1 : (mean <= 6.0 ? 4 : (mean <= 12.0 ? 8 : (mean <= 24.0 ? 16 : 32)));
     }
-    std::vector<int32_t> perm((size_t)n), fill(info.level_ptr.begin(), info.level_ptr.end() - 1);
-    for (int64_t i = 0; i < n; i++) perm[(size_t)fill[(size_t)lev[(size_t)i]]++] = (int32_t)i;
+    info.pos.reset(new int32_t[(size_t)n]);
+    for (int64_t i = 0; i < n; i++) {
+        const int32_t at = fill[(size_t)lev[(size_t)i]]++;
+        perm[(size_t)at] = (int32_t)i;
+        info.pos[(size_t)i] = at;
+    }
     HIPCHK(c, hipMalloc(&info.d_perm, (size_t)n * 4));
-    hipError_t e = hipMemcpy(info.d_perm, perm.data(), (size_t)n * 4, hipMemcpyHostToDevice);
+    hipError_t e = hipMemcpy(info.d_perm, perm.get(), (size_t)n * 4, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         (void)hipFree(info.d_perm);
         return hip_fail(c, e);
     }
-    info.perm = std::move(perm);
     auto res = c->levels.emplace(key, std::move(info));
     *out = &res.first->second;
     return SILU_OK;
@@ -1184,8 +1196,7 @@ int build_level_layout(silu_ctx *c, const silu_csr *T, LevelInfo *li)
     const int64_t n = T->n_rows;
     const int depth = li->depth;
     li->tried = true;
-    std::vector<int32_t> perm;
-    perm.swap(li->perm);
+    const std::unique_ptr<int32_t[]> pos = std::move(li->pos);
     std::vector<double> weight((size_t)depth);
     double least = pack_us(T->nnz); // before the ring's limit on runs is known
     const double csr_total = csr_us((double)T->nnz / (double)n) * depth;
@@ -1206,9 +1217,8 @@ int build_level_layout(silu_ctx *c, const silu_csr *T, LevelInfo *li)
         const hipError_t e = hipMalloc(dst, std::max<size_t>(bytes, 8));
         return e == hipSuccess && srcp ? hipMemcpyAsync(*dst, srcp, bytes, hipMemcpyHostToDevice, c->stream) : e;
     };
-    std::vector<int32_t> pos((size_t)n), reach((size_t)depth, -1), start((size_t)depth), counts((size_t)n * 2);
-    for (int64_t i = 0; i < n; i++) pos[(size_t)perm[(size_t)i]] = (int32_t)i;
-    HIPCHK(c, up(&tmp.p[0], pos.data(), pos.size() * 4));
+    std::vector<int32_t> reach((size_t)depth, -1), start((size_t)depth);
+    HIPCHK(c, up(&tmp.p[0], pos.get(), (size_t)n * 4));
     HIPCHK(c, up(&tmp.p[1], li->level_ptr.data(), li->level_ptr.size() * 4));
     HIPCHK(c, up(&tmp.p[2], reach.data(), reach.size() * 4));
     const int32_t *d_pos = (const int32_t *)tmp.p[0], *d_lp = (const int32_t *)tmp.p[1];
@@ -1251,10 +1261,13 @@ int build_level_layout(silu_ctx *c, const silu_csr *T, LevelInfo *li)
         return SILU_OK;
     }
     HIPCHK(c, up(&tmp.p[3], start.data(), start.size() * 4));
-    HIPCHK(c, up(&tmp.p[4], nullptr, counts.size() * 4));
+    HIPCHK(c, up(&tmp.p[4], nullptr, (size_t)n * 8));
     HIPCHK(c, launch_level_count((int)n, depth, d_lp, (const int32_t *)tmp.p[3], li->d_perm, d_pos, T->row_ptr, T->col_idx,
                                  (int32_t *)tmp.p[4], c->stream));
-    HIPCHK(c, hipMemcpyAsync(counts.data(), tmp.p[4], counts.size() * 4, hipMemcpyDeviceToHost, c->stream));
+    // near entries of every row, then far ones: a run from the first level on has none
+    const bool any_far = li->steps.size() > 1 || li->steps[0].wide;
+    std::unique_ptr<int32_t[]> counts(new int32_t[(size_t)n * (any_far ? 2 : 1)]);
+    HIPCHK(c, hipMemcpyAsync(counts.get(), tmp.p[4], (size_t)n * (any_far ? 8 : 4), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     // slices of one kind over a level's rows; a slice ends at 64 rows, or where its padding would come to
     // exceed three times its entries
@@ -1286,7 +1299,7 @@ int build_level_layout(silu_ctx *c, const silu_csr *T, LevelInfo *li)
                 longest = sum = 0;
             }
             if (alone) { // its 64 lanes take every 64th of the row's entries, of either kind
-                add(i, -1, (counts[(size_t)i] + counts[(size_t)(n + i)] + 1 + 63) / 64);
+                add(i, -1, (counts[(size_t)i] + (any_far ? counts[(size_t)(n + i)] : 0) + 1 + 63) / 64);
                 r0 = i + 1;
                 continue;
             }
@@ -1301,7 +1314,7 @@ int build_level_layout(silu_ctx *c, const silu_csr *T, LevelInfo *li)
         s.f0 = (int)slices[1].size();
         for (int l = s.l0; l < s.l1; l++) {
             if (!s.wide) cut(0, l, true);
-            cut(1, l, s.wide);
+            if (s.l0 > 0 || s.wide) cut(1, l, s.wide);
             first[(size_t)l + 1] = (int32_t)slices[0].size();
         }
         s.f1 = (int)slices[1].size();
