@@ -151,7 +151,6 @@ struct StepPlan {
     int count[5] = {0, 0, 0, 0, 0};
     StagedGroup sg[5];
     int nsg = 0;
-    std::vector<uint8_t> grouped; // the op may share a workgroup: row patterns, no check
     std::vector<int> order;       // group_ops: the ops of one precision, those on one matrix together
     std::vector<int32_t> start;   // and the first op of each group
 };
@@ -808,13 +807,10 @@ void plan_step(const silu_server *s, int t, StepPlan &p)
     p.nsg = 0;
     p.ops.resize((size_t)nops);
     p.prec.resize((size_t)nops);
-    p.grouped.resize((size_t)nops);
     for (int i = 0; i < nops; i++) {
         Request q = s->active[(size_t)i];
         q.op += t;
-        const SweepArgs a = p.ops[(size_t)i] = op_of(s, q, &p.prec[(size_t)i]);
-        const Matrix &M = s->mats[(size_t)q.mid];
-        p.grouped[(size_t)i] = a.sv && M.patterns[a.sv - M.d_views] && !a.scheck;
+        p.ops[(size_t)i] = op_of(s, q, &p.prec[(size_t)i]);
     }
     for (int g = 0; g < 5; g++) p.count[g] = 0;
     for (int i = 0; i < nops; i++)
@@ -847,7 +843,7 @@ bool plan_staged(const StepPlan &p)
 // ops meet), so groups are made where they save half of a launch's workgroups.
 constexpr int64_t GROUP_TILES = 1536;
 constexpr int64_t GROUP_SAVES = 2;
-int group_ops(StepPlan &p, Prec kind, int32_t *first)
+int group_ops(const silu_server *s, StepPlan &p, Prec kind, int32_t *first)
 {
     std::vector<int> &order = p.order;
     std::vector<int32_t> &start = p.start;
@@ -856,15 +852,22 @@ int group_ops(StepPlan &p, Prec kind, int32_t *first)
     int64_t tiles = 0;
     for (int i = 0; i < (int)p.ops.size(); i++) {
         if (p.prec[(size_t)i] != kind) continue;
+        first[order.size()] = (int32_t)tiles;
         order.push_back(i);
         tiles += (p.ops[(size_t)i].n + SERVE_RPB - 1) / SERVE_RPB;
     }
-    const int most = (int)std::min<int64_t>(std::max<int64_t>(tiles / GROUP_TILES, 1), GROUP_OPS);
-    auto copy = [&](int i) { return p.grouped[(size_t)i] ? p.ops[(size_t)i].sv : nullptr; };
+    first[order.size()] = (int32_t)tiles;
+    const int most = (int)std::min<int64_t>(tiles / GROUP_TILES, GROUP_OPS);
+    if (most <= 1) return (int)order.size(); // every op by itself
+    // what op i may share: row patterns, where it makes no check
+    auto copy = [&](int i) {
+        const SweepArgs &a = p.ops[(size_t)i];
+        const Matrix &M = s->mats[(size_t)s->active[(size_t)i].mid];
+        return a.sv && !a.scheck && M.patterns[a.sv - M.d_views] ? a.sv : nullptr;
+    };
     // groups first: a group's workgroups run as long as its ops, and would end the launch
-    if (most > 1)
-        std::stable_sort(order.begin(), order.end(),
-                         [&](int i, int j) { return std::less<const SlicedView *>()(copy(j), copy(i)); });
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int i, int j) { return std::less<const SlicedView *>()(copy(j), copy(i)); });
     const int k = (int)order.size();
     auto cut = [&](bool share) {
         int groups = 0, total = 0;
@@ -886,13 +889,13 @@ int group_ops(StepPlan &p, Prec kind, int32_t *first)
         start.push_back(k);
         return groups;
     };
-    int groups = cut(most > 1);
+    int groups = cut(true);
     if (groups < k && first[groups] * GROUP_SAVES > tiles) groups = cut(false);
     return groups;
 }
 
 // The plan's staged groups packed into buf from *used on.
-void pack_step(StepPlan &p, char *buf, size_t *used)
+void pack_step(const silu_server *s, StepPlan &p, char *buf, size_t *used)
 {
     for (int g = 0; g < 5; g++) {
         if (p.count[g] <= BATCH_ARG_OPS) continue;
@@ -900,7 +903,7 @@ void pack_step(StepPlan &p, char *buf, size_t *used)
         const size_t first_off = *used + sizeof(SweepArgs) * (size_t)k;
         SweepArgs *h_ops = (SweepArgs *)(buf + *used);
         int32_t *h_first = (int32_t *)(buf + first_off);
-        const int groups = group_ops(p, KINDS[g], h_first);
+        const int groups = group_ops(s, p, KINDS[g], h_first);
         for (int i = 0; i < k; i++) h_ops[i] = p.ops[(size_t)p.order[(size_t)i]];
         if (groups < k) std::copy(p.start.begin(), p.start.end(), h_first + groups + 1);
         p.sg[p.nsg++] = {KINDS[g], *used, first_off, k, h_first[groups], groups};
@@ -916,10 +919,10 @@ hipError_t launch_step(silu_server *s, StepPlan &p, const char *d_stage)
     for (int g = 0; g < 5 && e == hipSuccess; g++) {
         if (!p.count[g] || p.count[g] > BATCH_ARG_OPS) continue;
         BatchArgs ba;
-        ba.groups = group_ops(p, KINDS[g], ba.first);
+        ba.groups = group_ops(s, p, KINDS[g], ba.first);
         ba.nops = p.count[g];
         for (int i = 0; i < ba.nops; i++) ba.op[i] = p.ops[(size_t)p.order[(size_t)i]];
-        std::copy(p.start.begin(), p.start.end(), ba.start);
+        if (ba.groups < ba.nops) std::copy(p.start.begin(), p.start.end(), ba.start);
         e = launch_sweep_batch_args(KINDS[g], ba, s->stream);
     }
     for (int i = 0; i < p.nsg && e == hipSuccess; i++) {
@@ -1019,7 +1022,7 @@ int burst(silu_server *s, int k_max, int *done)
         if ((st = claim_mark(s, &slot))) return st; // its staging buffer is free
     }
     size_t used = 0;
-    for (int t = 0; t < k && staged; t++) pack_step(plans[(size_t)t], s->h_stage[slot], &used);
+    for (int t = 0; t < k && staged; t++) pack_step(s, plans[(size_t)t], s->h_stage[slot], &used);
     hipError_t e = hipSuccess;
     if (used) e = hipMemcpyAsync(s->d_stage, s->h_stage[slot], used, hipMemcpyHostToDevice, s->stream);
     for (int t = 0; t < k && e == hipSuccess; t++) e = launch_step(s, plans[(size_t)t], s->d_stage);
@@ -1111,7 +1114,7 @@ int silu_server_step(silu_server *s, int *n_active, int *n_queued)
         int slot = -1;
         if (staged && (st = claim_mark(s, &slot))) return st; // its staging buffer is free
         size_t used = 0;
-        if (staged) pack_step(p, s->h_stage[slot], &used);
+        if (staged) pack_step(s, p, s->h_stage[slot], &used);
         hipError_t e = hipSuccess;
         if (used) e = hipMemcpyAsync(s->d_stage, s->h_stage[slot], used, hipMemcpyHostToDevice, s->stream);
         if (e == hipSuccess) e = launch_step(s, p, s->d_stage);
