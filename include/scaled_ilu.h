@@ -523,7 +523,7 @@ int trisolve_iter(silu_ctx *ctx, const silu_csr *T, const double *dinv, const do
 int silu_analyze(silu_ctx *ctx, const silu_csr *T, int uplo, int32_t *depth, int32_t *rows_per_level);
 
 /* Drop everything the context cached for the matrix whose row_ptr or
- * col_idx is given (level sets and their layouts, row-block partitions,
+ * col_idx is given (level sets, their layouts and graphs, row-block partitions,
  * 16-bit codes, sliced copies).  The caches are keyed by pointers and sizes,
  * so call this before freeing a matrix, or changing its pattern or (for the
  * sliced copies) its values in place.  Synchronizes the context stream. */
